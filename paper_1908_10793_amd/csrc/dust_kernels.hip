@@ -66,17 +66,23 @@ __global__ void __launch_bounds__(256) k_gather(PView<TS> p, const Box* boxes, i
   if (nc > 2 && vg2) vg2[i] = TW(v[2]);
 }
 
+// Workgroups of the kick: a grid-stride loop, so that the diagnostic sums
+// take one set of atomics per workgroup.  One per wave, as before, had 64
+// particles share five contended FP64 atomics: 6.5 ms for 8.5 M particles,
+// of which the particles' own traffic is 0.1 ms.
+static constexpr int KICK_BLOCKS = 1024;
+
 template <typename TS, typename A, typename TW, int GEOM, int NDIM, bool U>
 __global__ void __launch_bounds__(256) k_kick(PView<TS> p, const Box* boxes, int nbox, Forces f,
                                               const Species* sp, int drag_mode, A dt, const TW* rho_p,
                                               const TW* vg0,
                                               const TW* vg1, const TW* vg2, TW* imp0, TW* imp1,
                                               TW* imp2, TW* imp3, DiagDev* dg, double* part) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   constexpr int nc = GEOM == GEOM_CART ? NDIM : 3;
   double sums[5] = {0, 0, 0, 0, 0};
   double cells = 0.0;
-  if (i < p.n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n; i += stride) {
     int idx[3];
     A off[3], mom[3];
     int b = load_particle<TS, A, GEOM, NDIM>(p, boxes, nbox, i, idx, off, mom, dg);
@@ -113,37 +119,36 @@ __global__ void __launch_bounds__(256) k_kick(PView<TS> p, const Box* boxes, int
         fin &= isfinite(double(mom[k]));
         p.mom[k][i] = TS(mom[k]);
         if (imp[k]) imp[k][i] = TW(m * o.j[k]);
-        sums[k] = double(m * o.j[k]);
+        sums[k] += double(m * o.j[k]);
         sums[4] += fabs(double(m * o.j[k]));
       }
       if (imp[nc]) imp[nc][i] = TW(m * o.e);
-      sums[3] = double(m * o.e);
+      sums[3] += double(m * o.e);
       if (!fin) flag(dg, DUST_FLAG_NONFINITE);
     }
   }
   if (dg) {
+    __shared__ double red[4][6];
 #pragma unroll
     for (int k = 0; k < 5; ++k) sums[k] = wave_sum(sums[k]);
     cells = wave_max(cells);
-    if (part) {
-      // deterministic: the block's sums in a fixed order into its slot of
-      // part (added up by k_reduce_kick_partials)
-      __shared__ double red[4][5];
-      if ((threadIdx.x & 63) == 0)
-        for (int k = 0; k < 5; ++k) red[threadIdx.x >> 6][k] = sums[k];
-      __syncthreads();
-      if (threadIdx.x < 5)
-        part[(size_t)blockIdx.x * 5 + threadIdx.x] =
-            ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
-    }
     if ((threadIdx.x & 63) == 0) {
-      if (!part) {
-        for (int k = 0; k < 3; ++k) unsafeAtomicAdd(&dg->p_part[k], sums[k]);
-        unsafeAtomicAdd(&dg->e_part, sums[3]);
-        unsafeAtomicAdd(&dg->sum_abs_j, sums[4]);
-      }
-      atomic_max_nonneg(&dg->max_cells_bits, cells);
-      if (cells > 1.8) atomicOr(&dg->flags, (unsigned)DUST_FLAG_CFL);
+      for (int k = 0; k < 5; ++k) red[threadIdx.x >> 6][k] = sums[k];
+      red[threadIdx.x >> 6][5] = cells;
+    }
+    __syncthreads();
+    // the block's sums in a fixed order: into its slot of part (deterministic,
+    // added up by k_reduce_kick_partials), else to the diagnostics
+    if (threadIdx.x < 5) {
+      const int k = threadIdx.x;
+      const double v = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+      if (part) part[(size_t)blockIdx.x * 5 + k] = v;
+      else unsafeAtomicAdd(k < 3 ? &dg->p_part[k] : k == 3 ? &dg->e_part : &dg->sum_abs_j, v);
+    }
+    if (threadIdx.x == 0) {
+      const double c = fmax(fmax(red[0][5], red[1][5]), fmax(red[2][5], red[3][5]));
+      atomic_max_nonneg(&dg->max_cells_bits, c);
+      if (c > 1.8) atomicOr(&dg->flags, (unsigned)DUST_FLAG_CFL);
     }
   }
 }
@@ -1095,16 +1100,19 @@ void launch_kick(const PView<TS>& p, const Box* boxes, int nbox, int geom, int n
                  const TW* const vg[3], TW* const imp[4], DiagDev* dg, double* part, hipStream_t st) {
   if (p.n == 0) return;
   if (!dg) part = nullptr;
+  const unsigned nb = std::min<unsigned>(blocks_for(p.n), KICK_BLOCKS);
   DUST_GEOM_SWITCH(geom, ndim, unif,
-                   hipLaunchKernelGGL((k_kick<TS, A, TW, G_, D_, U_>), dim3(blocks_for(p.n)), dim3(256),
+                   hipLaunchKernelGGL((k_kick<TS, A, TW, G_, D_, U_>), dim3(nb), dim3(256),
                                       0, st, p, boxes, nbox, f, sp, drag_mode, A(dt), rho_p, vg[0], vg[1],
                                       vg[2], imp[0], imp[1], imp[2], imp[3], dg, part));
   if (part)
     hipLaunchKernelGGL(k_reduce_kick_partials, dim3(1), dim3(256), 0, st, (const double*)part,
-                       (int64_t)blocks_for(p.n), dg);
+                       (int64_t)nb, dg);
 }
 
-int64_t kick_partial_words(int64_t n) { return 5 * (int64_t)blocks_for(std::max<int64_t>(n, 1)); }
+int64_t kick_partial_words(int64_t n) {
+  return 5 * (int64_t)std::min<unsigned>(blocks_for(std::max<int64_t>(n, 1)), KICK_BLOCKS);
+}
 
 template <typename TS, typename A, typename TW>
 void launch_deposit(const PView<TS>& p, const Box* boxes, int nbox, int geom, int ndim, int unif,
