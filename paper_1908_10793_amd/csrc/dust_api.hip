@@ -348,8 +348,10 @@ dust_status_t check_fields(Ctx* c, const dust_fields_t* f, bool gas, bool dep) {
   return DUST_OK;
 }
 
-dust_status_t ensure_ws(Ctx* c, int64_t n) {
-  size_t need = (size_t)std::max<int64_t>(n, 1) * 8 * 8;
+// Workspace of the unfused step and the deterministic sources: words of 8
+// bytes per particle.
+dust_status_t ensure_ws(Ctx* c, int64_t n, int words = 8) {
+  size_t need = (size_t)std::max<int64_t>(n, 1) * words * 8;
   if (need <= c->ws_bytes) return DUST_OK;
   if (c->ws) HIP_TRY(hipFree(c->ws));
   c->ws = nullptr;
@@ -599,10 +601,11 @@ void source_det(Ctx* c, const PView<TS>& pv, const FView<TS>& fl, const FView<TS
 // One of the sums of dust_sorted.h, after sorting the particles by tile (the
 // binned layout of a fused run, which bin_start describes, stays as it is).
 template <typename TS, typename A, typename TW, int MODE>
-void run_sorted(Ctx* c, const PView<TS>& pv, const FView<TS>& fl, const SortedIn<TW>& in, const double* xg,
+void run_sorted(Ctx* c, const PView<TS>& pv, const FView<TS>& fl, const SortedIn<TS, TW>& in, const double* xg,
                 const Forces& F, double dt, hipStream_t st) {
+  // (the step's first drift wrote the keys)
   c->bin_cur = launch_bin(pv.cell, pv.n, c->boxes_d, c->nbox, c->n_active, DUST_BIN_TILE,
-                          sorted_tile(sizeof(A) == 8, c->ndim), c->bin, nullptr, nullptr, false, st);
+                          sorted_tile(c->ndim), c->bin, nullptr, nullptr, MODE == SORTED_STEP, st);
   launch_sorted<TS, A, TW, MODE>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fl, in, xg, F, c->species_d,
                                  c->drag_mode, dt, c->bin.key[c->bin_cur], c->bin.val[c->bin_cur], c->n_active,
                                  c->diag, true, st);
@@ -637,12 +640,19 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
   if (!(flags & DUST_STEP_NO_FILL))
     launch_fill<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, c->xg, st);
   launch_clear_deposits<TS>(fv, nc + 1, c->n_stored, st);
-  launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, 0.5 * dt, 1, dflags, st);
   const double* xg = (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg;
   if (c->step_sorted) {
-    if constexpr (std::is_same<A, double>::value)
-      run_sorted<TS, A, TS, SORTED_STEP>(c, pv, fv, SortedIn<TS>{}, xg, F, dt, st);
+    if constexpr (std::is_same<A, double>::value) {
+      StepRecord<TS>* rec = (StepRecord<TS>*)c->ws;
+      launch_step_pack<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, 0.5 * dt, rec,
+                              c->bin.key[0], c->n_active, dflags, st);
+      run_sorted<TS, A, TS, SORTED_STEP>(c, pv, fv, SortedIn<TS, TS>{{}, rec}, xg, F, dt, st);
+      launch_step_unpack<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, rec,
+                                dflags, st);
+    }
   } else {
+    launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, 0.5 * dt, 1, dflags,
+                        st);
     launch_gather<TS, A, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fv, xg, rho_p, vg, dflags, st);
     const A* cvg[3] = {vg[0], vg[1], vg[2]};
     launch_kick<TS, A, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, c->species_d, c->drag_mode, dt,
@@ -652,8 +662,8 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
       deposit_det<TS, A, A>(c, pv, fv, cimp, st);
     else
       launch_deposit<TS, A, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fv, cimp, dflags, st);
+    launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dflags, st);
   }
-  launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dflags, st);
   if (dg)
     launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, st);
   launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, st);
@@ -1241,7 +1251,7 @@ dust_status_t dust_deposit(void* ctx, const dust_particles_t* p, const void* con
       deposit_det<TS, A, TS>(c, pview<TS>(p), fview<TS>(f), imp, st);
     else if (sorted_sums(c, p->n, st))
       run_sorted<TS, A, TS, SORTED_DEPOSIT>(c, pview<TS>(p), fview<TS>(f),
-                                            SortedIn<TS>{{imp[0], imp[1], imp[2], imp[3]}}, nullptr, Forces{}, 0.0,
+                                            SortedIn<TS, TS>{{imp[0], imp[1], imp[2], imp[3]}, nullptr}, nullptr, Forces{}, 0.0,
                                             st);
     else
       launch_deposit<TS, A, TS>(pview<TS>(p), c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fview<TS>(f), imp,
@@ -1286,7 +1296,7 @@ dust_status_t dust_drag_source(void* ctx, const dust_particles_t* p, dust_fields
       }
     }
     if (sorted_sums(c, p->n, st)) {
-      run_sorted<TS, A, TS, SORTED_SOURCE>(c, pview<TS>(p), fview<TS>(f), SortedIn<TS>{}, nullptr, F, 1.0 / dt, st);
+      run_sorted<TS, A, TS, SORTED_SOURCE>(c, pview<TS>(p), fview<TS>(f), SortedIn<TS, TS>{}, nullptr, F, 1.0 / dt, st);
       HIP_TRY(hipGetLastError());
       return DUST_OK;
     }
@@ -1334,7 +1344,7 @@ dust_status_t dust_deposit_mass(void* ctx, const dust_particles_t* p, void* rho_
     if (sorted_sums(c, p->n, st)) {
       FView<TS> out{};
       out.dep[0] = (TS*)rho_d;
-      run_sorted<TS, A, TS, SORTED_MASS>(c, pview<TS>(p), out, SortedIn<TS>{}, nullptr, Forces{}, 0.0, st);
+      run_sorted<TS, A, TS, SORTED_MASS>(c, pview<TS>(p), out, SortedIn<TS, TS>{}, nullptr, Forces{}, 0.0, st);
       HIP_TRY(hipGetLastError());
       return DUST_OK;
     }
@@ -1383,13 +1393,19 @@ dust_status_t dust_step(void* ctx, dust_particles_t* p, dust_fields_t* f, double
     flags &= ~DUST_STEP_FUSED;
     if ((s = ensure_det(c, p->n))) return s;
   }
-  c->step_sorted = !c->det && !(flags & DUST_STEP_FUSED) && sorted_sums(c, p->n, st);
-  // (the sorted sums need no further workspace, but the same call under the
-  // caller's capture does: kept ready where it can be had)
-  if (!(flags & DUST_STEP_FUSED) && (s = ensure_ws(c, p->n))) {
-    if (!c->step_sorted) return s;
-    (void)hipGetLastError();
-    g_err.clear();
+  // the unfused step: over sorted particles, their state in packed records
+  // (FP64: 80 bytes each, at least the 8 words of the other chain), or else
+  // kernel by kernel through 8 words of workspace per particle
+  c->step_sorted = false;
+  if (!(flags & DUST_STEP_FUSED)) {
+    if (!c->det && sorted_sums(c, p->n, st)) {
+      c->step_sorted = ensure_ws(c, p->n, c->prec == DUST_F64 ? 10 : 8) == DUST_OK;
+      if (!c->step_sorted) {
+        (void)hipGetLastError();
+        g_err.clear();
+      }
+    }
+    if (!c->step_sorted && (s = ensure_ws(c, p->n))) return s;
   }
   if (flags & DUST_STEP_FUSED) {
     if (frc->integrator != DUST_INTEGRATOR_EXPMID)

@@ -6,6 +6,6 @@ namespace dust {
 DUST_SORTED_INST(float, double, float, SORTED_DEPOSIT)
 DUST_SORTED_INST(float, double, float, SORTED_SOURCE)
 DUST_SORTED_INST(float, double, float, SORTED_MASS)
-DUST_SORTED_INST(float, double, float, SORTED_STEP)
+DUST_SORTED_STEP_INST(float, double)
 
 }  // namespace dust

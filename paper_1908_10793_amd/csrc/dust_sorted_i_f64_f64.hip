@@ -6,6 +6,6 @@ namespace dust {
 DUST_SORTED_INST(double, double, double, SORTED_DEPOSIT)
 DUST_SORTED_INST(double, double, double, SORTED_SOURCE)
 DUST_SORTED_INST(double, double, double, SORTED_MASS)
-DUST_SORTED_INST(double, double, double, SORTED_STEP)
+DUST_SORTED_STEP_INST(double, double)
 
 }  // namespace dust

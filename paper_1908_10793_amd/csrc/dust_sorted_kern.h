@@ -10,18 +10,20 @@
 // share a cell, and its adds queue on the same words).  Here
 //  * a workgroup takes a fixed number of consecutive slots of the sorted
 //    order, whatever their cells hold (no imbalance where dust collects),
-//    and walks them tile by tile with an FP64 LDS window over the tile and
-//    one cell around it;
-//  * one lane per particle loads it, forms its weights and its channels'
-//    values and puts them in LDS; then half a wave (a quarter in 2-D) takes
-//    the particles one after the other, one lane per cell of the stencil,
-//    and sums in registers until the host cell changes.  A lane holds one
-//    cell's channels (4 registers where a thread per host cell needs 108),
-//    so FP64 sums cost no occupancy, and lanes never wait for the fullest
-//    cell of a wave;
-//  * a run of one host cell is then added to the window (27 lanes, 27
-//    words: no two lanes on one word), and the window to HBM once per tile.
+//    and walks them in chunks of 256, tile by tile, with an FP64 LDS window
+//    over the tile and one cell around it;
+//  * one lane per particle forms its weights and its channels' values and
+//    puts them in LDS (the next chunk's particles are loaded meanwhile);
+//    then nine lanes take a particle, one lane per row of three cells of its
+//    stencil (2-D: per cell), seven particles of a wave at a time, and sum in
+//    registers until the host cell changes.  A lane holds one row's channels
+//    (12 registers where a thread per host cell needs 108), so FP64 sums
+//    cost no occupancy, and lanes never wait for the fullest cell of a wave;
+//  * a run of one host cell is then added to the window, and the window to
+//    HBM once per tile.
 #pragma once
+
+#include <type_traits>
 
 #include "dust_device.h"
 #include "dust_launch.h"
@@ -32,143 +34,251 @@ namespace dust {
 
 static constexpr int SORTED_THREADS = 256;   // also the particles of a chunk
 
-template <typename A> struct GasCell { A v[4]; };   // three velocity components, density
+// Three velocity components and the density of a window's cell, in the
+// storage type; the unfused step in Cartesian boxes takes the arithmetic type
+// (the x ghosts of a shear-periodic box are FP64 values).
+template <typename T> struct GasCell { T v[4]; };
 
 // Compile-time layout of a kernel.
-template <typename A, int GEOM, int NDIM, int MODE> struct SortedShape {
+template <typename TS, typename A, int GEOM, int NDIM, int MODE> struct SortedShape {
   static constexpr int NC = GEOM == GEOM_CART ? NDIM : 3;
   static constexpr int NCH = MODE == SORTED_MASS ? 1 : MODE == SORTED_SOURCE ? NC : NC + 1;
   static constexpr bool GAS = MODE == SORTED_SOURCE || MODE == SORTED_STEP;
-  // the tile (FP64 with a gas window: half as long in x, so that three
-  // workgroups fit a CU's LDS)
-  static constexpr int T0 = sorted_tile_extent(sizeof(A) == 8, NDIM, 0);
-  static constexpr int T1 = sorted_tile_extent(sizeof(A) == 8, NDIM, 1);
-  static constexpr int T2 = sorted_tile_extent(sizeof(A) == 8, NDIM, 2);
+  using TG = typename std::conditional<MODE == SORTED_STEP && GEOM == GEOM_CART, A, TS>::type;
+  static constexpr int T0 = sorted_tile_extent(NDIM, 0), T1 = sorted_tile_extent(NDIM, 1),
+                       T2 = sorted_tile_extent(NDIM, 2);
   static constexpr int RX = T0 + 2, RY = T1 + 2, RZ = NDIM > 2 ? T2 + 2 : 1;
   static constexpr int WC = RX * RY * RZ;
   static constexpr int NT = NDIM > 2 ? 27 : 9;    // cells of a stencil
-  static constexpr int G = NDIM > 2 ? 32 : 16;    // lanes (and particles of a chunk) of a group
-  // one particle's words: FP32 q[4], w0[3], w1 w2 products[9] at 20 words
-  // (consecutive lanes' 16-byte writes on distinct banks); FP64 q[4], w0[3],
-  // w1[3], w2[3] at 14 (the same, with less LDS)
-  static constexpr int RS = sizeof(A) == 4 ? 20 : 14;
-  // the groups of a wave read at the same time: shifted by half (a quarter)
-  // of the 64 banks
-  static constexpr int GP = (NDIM > 2 ? 32 : 16) / (int)(sizeof(A) / 4);
-  static constexpr int GS = G * RS + GP;
+  // a stencil over 9 lanes: a row of NA = 3 cells each (2-D: one cell)
+  static constexpr int NA = NDIM > 2 ? 3 : 1;
+  static constexpr int GROUPS = 7;                // particles that a wave takes at a time
+  // a wave's 64 particles go through its records in one round, FP64 in two
+  // (with the records of 64, one workgroup less would fit a CU's LDS)
+  static constexpr int ROUNDS = sizeof(A) == 4 ? 1 : 2;
+  static constexpr int RP = 64 / ROUNDS;          // particles of a round
+  static constexpr int PG = (RP + GROUPS - 1) / GROUPS;   // a group's share of them
+  // one particle's words: q[4], w0[3] and a pad, then FP32 the 9 products w1
+  // w2 at a stride of 20 words, FP64 w1[3], w2[3] at 14 (no pad): consecutive
+  // lanes' 16-byte writes, and the seven groups' reads, on distinct banks
+  static constexpr bool F32 = sizeof(A) == 4;
+  static constexpr int RS = F32 ? 20 : 14;
+  static constexpr int W0 = 4, W1 = F32 ? 8 : 7, W2 = 10;
+  static constexpr int WR = GROUPS * PG;          // records of a wave (those past RP stay zero)
 };
 
+// A wave's LDS writes before this, its reads after (its LDS operations
+// complete in order; this keeps the compiler's order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Stored state of one particle, as loaded a chunk ahead.
+template <typename TS, typename TW> struct SortedRaw {
+  int32_t cell, species;
+  TS off[3], mom[3], drag, mass;
+  TW q[4];
+};
+
+template <typename TS, typename TW, int GEOM, int NDIM, int MODE>
+__device__ __forceinline__ void sorted_load(const PView<TS>& p, const SortedIn<TS, TW>& in, int drag_mode, int64_t i,
+                                            SortedRaw<TS, TW>& r) {
+  constexpr int NC = GEOM == GEOM_CART ? NDIM : 3;
+  if constexpr (MODE == SORTED_STEP) {
+    // the packed record of the unfused step: one line of memory per particle
+    const StepRecord<TS> s = in.rec[i];
+    r.cell = s.cell;
+    r.species = s.species;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      r.off[d] = s.off[d];
+      r.mom[d] = s.mom[d];
+    }
+    r.drag = s.drag;
+    r.mass = s.mass;
+    return;
+  }
+  r.cell = p.cell[i];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    r.off[d] = d < NDIM ? p.off[d][i] : TS(0);
+    // (the deposit reads momenta only to flag non-finite ones, where given)
+    r.mom[d] = MODE != SORTED_MASS && d < NC && (MODE != SORTED_DEPOSIT || p.mom[d]) ? p.mom[d][i] : TS(0);
+  }
+  r.species = 0;
+  r.mass = r.drag = TS(0);
+  if constexpr (MODE == SORTED_DEPOSIT) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r.q[m] = m <= NC ? in.q[m][i] : TW(0);
+  } else {
+    if (p.species) r.species = p.species[i];
+    if (p.mass) r.mass = p.mass[i];
+    if (MODE != SORTED_MASS && drag_mode != DRAG_SPECIES) r.drag = p.drag[i];
+  }
+}
+
 template <typename TS, typename A, typename TW, int GEOM, int NDIM, bool U, int MODE>
-__global__ void __launch_bounds__(SORTED_THREADS)
-    k_sorted(PView<TS> p, const Box* __restrict__ boxes, int nbox, FView<TS> fl, SortedIn<TW> in,
+__global__ void __launch_bounds__(SORTED_THREADS) __attribute__((amdgpu_waves_per_eu(MODE == SORTED_STEP ? 2 : 1)))
+    k_sorted(PView<TS> p, const Box* __restrict__ boxes, int nbox, FView<TS> fl, SortedIn<TS, TW> in,
              const double* __restrict__ xg, Forces f, const Species* __restrict__ sp, int drag_mode, A dt,
              const uint32_t* __restrict__ key, const uint32_t* __restrict__ perm, uint32_t nbins, int ppb,
              DiagDev* dg, int sums) {
-  using S = SortedShape<A, GEOM, NDIM, MODE>;
-  constexpr int NC = S::NC, NCH = S::NCH, NT = S::NT, G = S::G, RX = S::RX, RY = S::RY, WC = S::WC;
+  using S = SortedShape<TS, A, GEOM, NDIM, MODE>;
+  using TG = typename S::TG;
+  constexpr int NC = S::NC, NCH = S::NCH, NA = S::NA, PG = S::PG, RX = S::RX, RY = S::RY, WC = S::WC;
   constexpr int c2 = NDIM > 2 ? 1 : 0;
-  constexpr bool F32 = sizeof(A) == 4;
+  constexpr bool F32 = S::F32;
   __shared__ double win[NCH * WC];
-  __shared__ __align__(16) A rec[(SORTED_THREADS / G) * S::GS];
+  __shared__ __align__(16) A rec[(SORTED_THREADS / 64) * S::WR * S::RS];
   __shared__ int s_r[SORTED_THREADS];
-  __shared__ GasCell<A> gas[S::GAS ? WC : 1];
-  const int tid = threadIdx.x;
+  __shared__ GasCell<TG> gas[S::GAS ? WC : 1];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int64_t s0 = (int64_t)blockIdx.x * ppb;
   const int64_t s1 = s0 + ppb < p.n ? s0 + ppb : p.n;
   uint32_t flags = 0;
   double sum[5] = {0, 0, 0, 0, 0}, cells = 0.0;   // SORTED_STEP: the kick's diagnostics
-  // this lane's cell of the stencil, relative to the host cell
-  const int grp = tid / G, s = tid % G, sc_ = s < NT ? s : 0;
-  const int sa = sc_ % 3, sb = (sc_ / 3) % 3, scc = NDIM > 2 ? sc_ / 9 : 0;
-  const int soff = (sa - 1) + RX * ((sb - 1) + RY * (scc - c2));
+  // this lane's row of the stencil (2-D: cell), relative to the host cell
+  const int grp = lane / 9, row = lane % 9;
+  const bool sums_lane = grp < S::GROUPS;
+  const int rb = NDIM > 2 ? row % 3 : row / 3, rc = NDIM > 2 ? row / 3 : 0;   // y and z of the row
+  const int ra = NDIM > 2 ? 0 : row % 3;                                      // x of its first cell
+  const int soff = (ra - 1) + RX * ((rb - 1) + RY * (rc - c2));
+  // the records past a round's particles stay zero
+  for (int r = lane; r < (S::WR - S::RP) * S::RS; r += 64) rec[(wave * S::WR + S::RP) * S::RS + r] = A(0);
 
-  int64_t cur = s0;
-  while (cur < s1) {
-    const uint32_t k0 = key[cur];
-    if (k0 >= nbins) {
-      // sorted last: particles without a cell, and cell ids out of range
-      for (int64_t e = cur + tid; e < s1; e += SORTED_THREADS)
-        if (p.cell[perm[e]] >= 0) flags |= DUST_FLAG_BAD_CELL;
-      break;
-    }
-    // the tile of this key (its cells are consecutive keys)
-    const int ub = __builtin_amdgcn_readfirstlane(nbox == 1 ? 0 : find_box(boxes, nbox, k0));
+  // the tile in the window: its box, cells, first window cell, end of its keys
+  int ub = 0, e0 = 0, e1 = 0, e2 = 0, o0 = 0, o1 = 0, o2 = 0;
+  uint32_t kend = 0;
+  auto window_to_grid = [&]() {
     const Box& B = boxes[ub];
-    const int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = NDIM > 2 ? B.ax[2].n : 1;
-    int ti, tj, tk, e0, e1, e2;
-    uint32_t kend;
-    {
-      uint32_t r = k0 - (uint32_t)B.cell_base;
-      const uint32_t layer = (uint32_t)n0 * (uint32_t)n1 * (uint32_t)min(S::T2, n2);   // (at most the box)
-      tk = NDIM > 2 ? (int)(r / layer) : 0;
-      r -= (uint32_t)tk * layer;
-      e2 = min(S::T2, n2 - tk * S::T2);
-      const uint32_t row = (uint32_t)n0 * (uint32_t)min(S::T1, n1) * (uint32_t)e2;
-      tj = (int)(r / row);
-      r -= (uint32_t)tj * row;
-      e1 = min(S::T1, n1 - tj * S::T1);
-      const uint32_t col = (uint32_t)S::T0 * (uint32_t)(e1 * e2);
-      ti = (int)(r / col);
-      r -= (uint32_t)ti * col;
-      e0 = min(S::T0, n0 - ti * S::T0);
-      kend = k0 - r + (uint32_t)(e0 * e1 * e2);
-    }
-    const int o0 = ti * S::T0 - 1, o1 = tj * S::T1 - 1, o2 = tk * S::T2 - c2;   // window origin
     for (int r = tid; r < WC; r += SORTED_THREADS) {
+      const int a = r % RX, b = (r / RX) % RY, c = r / (RX * RY);
+      if (a >= e0 + 2 || b >= e1 + 2 || (NDIM > 2 && c >= e2 + 2)) continue;
+      const int64_t id = stored_index(B, o0 + a, o1 + b, o2 + c);
+      const double iv = inv_volume(B, o0 + a, o1 + b, o2 + c);
 #pragma unroll
-      for (int m = 0; m < NCH; ++m) win[m * WC + r] = 0.0;
-      if constexpr (S::GAS) {
-        const int a = r % RX, b = (r / RX) % RY, c = r / (RX * RY);
-        GasCell<A> g{};
-        if (a < e0 + 2 && b < e1 + 2 && (NDIM < 3 || c < e2 + 2)) {
-#pragma unroll
-          for (int m = 0; m < NC; ++m) g.v[m] = A(gas_comp(B, fl, xg, m, o0 + a, o1 + b, o2 + c));
-          if (drag_mode == DRAG_EPSTEIN) g.v[3] = A(fl.rho[stored_index(B, o0 + a, o1 + b, o2 + c)]);
-        }
-        gas[r] = g;
+      for (int m = 0; m < NCH; ++m) {
+        const double x = win[m * WC + r];
+        if (x != 0.0) unsafeAtomicAdd(&fl.dep[m][id], TS(x * iv));
       }
     }
-    // chunks of 256 slots while they stay in the tile
-    for (;;) {
-      const int64_t e = cur + tid;
-      const bool has = e < s1 && key[e < s1 ? e : s1 - 1] < kend;
-      const int cnt = __syncthreads_count(has);   // (sorted: the first cnt threads)
-      if (cnt == 0) break;
+  };
+  auto next_tile = [&](uint32_t k0) {
+    // the tile of key k0 (its cells are consecutive keys), its window
+    ub = __builtin_amdgcn_readfirstlane(nbox == 1 ? 0 : find_box(boxes, nbox, k0));
+    const Box& B = boxes[ub];
+    const int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = NDIM > 2 ? B.ax[2].n : 1;
+    uint32_t r = k0 - (uint32_t)B.cell_base;
+    const uint32_t layer = (uint32_t)n0 * (uint32_t)n1 * (uint32_t)min(S::T2, n2);   // (at most the box)
+    const int tk = NDIM > 2 ? (int)(r / layer) : 0;
+    r -= (uint32_t)tk * layer;
+    e2 = min(S::T2, n2 - tk * S::T2);
+    const uint32_t line = (uint32_t)n0 * (uint32_t)min(S::T1, n1) * (uint32_t)e2;
+    const int tj = (int)(r / line);
+    r -= (uint32_t)tj * line;
+    e1 = min(S::T1, n1 - tj * S::T1);
+    const uint32_t col = (uint32_t)S::T0 * (uint32_t)(e1 * e2);
+    const int ti = (int)(r / col);
+    r -= (uint32_t)ti * col;
+    e0 = min(S::T0, n0 - ti * S::T0);
+    kend = k0 - r + (uint32_t)(e0 * e1 * e2);
+    o0 = ti * S::T0 - 1;
+    o1 = tj * S::T1 - 1;
+    o2 = tk * S::T2 - c2;
+    for (int w = tid; w < WC; w += SORTED_THREADS) {
+#pragma unroll
+      for (int m = 0; m < NCH; ++m) win[m * WC + w] = 0.0;
+      if constexpr (S::GAS) {
+        const int a = w % RX, b = (w / RX) % RY, c = w / (RX * RY);
+        GasCell<TG> g{};
+        if (a < e0 + 2 && b < e1 + 2 && (NDIM < 3 || c < e2 + 2)) {
+#pragma unroll
+          for (int m = 0; m < NC; ++m) g.v[m] = TG(gas_comp(B, fl, xg, m, o0 + a, o1 + b, o2 + c));
+          if (drag_mode == DRAG_EPSTEIN) g.v[3] = TG(fl.rho[stored_index(B, o0 + a, o1 + b, o2 + c)]);
+        }
+        gas[w] = g;
+      }
+    }
+  };
+
+  // the particles of a chunk are loaded one chunk ahead, their places two
+  // (past the block's last slot: the last one again, not used)
+  auto slot = [&](int64_t e) { return e < s1 ? e : s1 - 1; };
+  SortedRaw<TS, TW> nxt;
+  uint32_t i_nxt = perm[slot(s0 + tid)], k_nxt = key[slot(s0 + tid)];
+  sorted_load<TS, TW, GEOM, NDIM, MODE>(p, in, drag_mode, i_nxt, nxt);
+  uint32_t i_far = perm[slot(s0 + SORTED_THREADS + tid)];
+  bool last = false;
+  for (int64_t cb = s0; cb < s1 && !last; cb += SORTED_THREADS) {
+    const SortedRaw<TS, TW> cur = nxt;
+    const uint32_t i = i_nxt, k = k_nxt;
+    const int nv = (int)(s1 - cb < SORTED_THREADS ? s1 - cb : SORTED_THREADS);
+    i_nxt = i_far;
+    k_nxt = key[slot(cb + SORTED_THREADS + tid)];
+    sorted_load<TS, TW, GEOM, NDIM, MODE>(p, in, drag_mode, i_nxt, nxt);
+    i_far = perm[slot(cb + 2 * SORTED_THREADS + tid)];
+    int done = 0;   // threads of the chunk whose particles are summed
+    while (done < nv) {
+      // those of the window's tile (sorted: threads done .. done + cnt - 1)
+      const bool has = tid >= done && tid < nv && k < kend;
+      const int cnt = __syncthreads_count(has);
+      if (cnt == 0) {
+        if (kend) window_to_grid();
+        const uint32_t k0 = key[cb + done];
+        if (k0 >= nbins) {
+          // sorted last: particles without a cell, and cell ids out of range
+          // (the step flagged those in its first drift)
+          if (MODE != SORTED_STEP)
+            for (int64_t e = cb + done + tid; e < s1; e += SORTED_THREADS)
+              if (p.cell[perm[e]] >= 0) flags |= DUST_FLAG_BAD_CELL;
+          kend = 0;
+          last = true;
+          break;
+        }
+        __syncthreads();   // (the window is cleared by other threads than read it)
+        next_tile(k0);
+        continue;
+      }
+      const Box& B = boxes[ub];
       int r0 = -1;
+      A q[4] = {A(0), A(0), A(0), A(0)};
+      Stencil<A> st;
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) st.w[d][a] = A(0);
       if (has) {
-        const int64_t i = perm[e];
-        const int64_t c = p.cell[i];
         int idx[3];
-        A off[3], mom[3] = {A(0), A(0), A(0)};
-        unravel(B, c - B.cell_base, idx);
+        A off[3], mom[3];
+        unravel(B, cur.cell - B.cell_base, idx);
         bool bad = false, nonfinite = false;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          off[d] = d < NDIM ? A(p.off[d][i]) : A(0);
+          off[d] = A(cur.off[d]);
           bad |= !(off[d] >= A(-0.5) && off[d] < A(0.5));
-          if (MODE != SORTED_MASS && d < NC && (S::GAS || p.mom[d])) mom[d] = A(p.mom[d][i]);
+          mom[d] = A(cur.mom[d]);
           nonfinite |= !isfinite(double(mom[d]));
         }
         flags |= bad ? (uint32_t)DUST_FLAG_OFFSET_RANGE : 0u;
         flags |= nonfinite ? (uint32_t)DUST_FLAG_NONFINITE : 0u;
         r0 = (idx[0] - o0) + RX * ((idx[1] - o1) + RY * (idx[2] - o2));
-        Stencil<A> st;
         stencil_weights<A, GEOM, NDIM, U>(B, idx, off, st);
-        A q[4] = {A(0), A(0), A(0), A(0)};
         if constexpr (MODE == SORTED_DEPOSIT) {
 #pragma unroll
-          for (int m = 0; m < NCH; ++m) q[m] = -A(in.q[m][i]);
+          for (int m = 0; m < NCH; ++m) q[m] = -A(cur.q[m]);
         } else {
-          int spc = p.species ? p.species[i] : 0;
+          int spc = cur.species;
           if (spc >= sp->n) {
             flags |= DUST_FLAG_BAD_CELL;
             spc = 0;
           }
-          const A m = p.mass ? A(p.mass[i]) : A(sp->mass[spc]);
+          const A m = p.mass ? A(cur.mass) : A(sp->mass[spc]);
           if constexpr (MODE == SORTED_MASS) {
             q[0] = m;
           } else {
-            const A dval = drag_mode == DRAG_SPECIES ? A(1) : A(p.drag[i]);
+            const A dval = drag_mode == DRAG_SPECIES ? A(1) : A(cur.drag);
             Where<A> w;
             where<A, GEOM, NDIM, U>(B, idx, off, w);
             // SOURCE: the slip as a weighted sum of differences; STEP: the
@@ -185,12 +295,12 @@ __global__ void __launch_bounds__(SORTED_THREADS)
 #pragma unroll
                 for (int a = -1; a <= 1; ++a) {
                   const A wt = st.w[0][a + 1] * wbc;
-                  const GasCell<A> g = gas[r0 + a + RX * (bb + RY * cc)];
-                  if (drag_mode == DRAG_EPSTEIN) rg += wt * g.v[3];
+                  const GasCell<TG> g = gas[r0 + a + RX * (bb + RY * cc)];
+                  if (drag_mode == DRAG_EPSTEIN) rg += wt * A(g.v[3]);
 #pragma unroll
                   for (int d = 0; d < NC; ++d) {
-                    if constexpr (MODE == SORTED_SOURCE) v[d] += wt * (g.v[d] * w.sc[d] - mom[d]);
-                    else v[d] += wt * g.v[d];
+                    if constexpr (MODE == SORTED_SOURCE) v[d] += wt * (A(g.v[d]) * w.sc[d] - mom[d]);
+                    else v[d] += wt * A(g.v[d]);
                   }
                 }
               }
@@ -199,9 +309,9 @@ __global__ void __launch_bounds__(SORTED_THREADS)
                              ? rg / dval
                              : inverse_tau<A, GEOM>(f, drag_mode, dval, A(sp->inv_tau[spc]), w);
             if constexpr (MODE == SORTED_SOURCE) {
-              const A k = m * (it < dt ? it : dt);   // dt: the reciprocal of the step here
+              const A kq = m * (it < dt ? it : dt);   // dt: the reciprocal of the step here
 #pragma unroll
-              for (int d = 0; d < NC; ++d) q[d] = -(k * v[d]);
+              for (int d = 0; d < NC; ++d) q[d] = -(kq * v[d]);
             } else {
               A sl[3] = {v[0] * w.sc[0] - mom[0], v[1] * w.sc[1] - mom[1], NC > 2 ? v[2] * w.sc[2] - mom[2] : A(0)};
               A c, psi;
@@ -217,7 +327,7 @@ __global__ void __launch_bounds__(SORTED_THREADS)
                 cells = cps > cells ? cps : cells;
                 mom[d] += o.dp[d];
                 fin &= isfinite(double(mom[d]));
-                p.mom[d][i] = TS(mom[d]);
+                in.rec[i].mom[d] = TS(mom[d]);
                 q[d] = -(m * o.j[d]);
                 sum[d] -= double(q[d]);
                 sum[4] += fabs(double(q[d]));
@@ -228,75 +338,88 @@ __global__ void __launch_bounds__(SORTED_THREADS)
             }
           }
         }
-        A* rw = rec + grp * S::GS + s * S::RS;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) rw[m] = q[m];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) rw[4 + a] = st.w[0][a];
-        if constexpr (F32) {
-#pragma unroll
-          for (int a = 0; a < 9; ++a) rw[7 + a] = st.w[1][a % 3] * st.w[2][NDIM > 2 ? a / 3 : 1];
-        } else {
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            rw[7 + a] = st.w[1][a];
-            rw[10 + a] = st.w[2][a];
-          }
-        }
       }
       s_r[tid] = r0;
-      __syncthreads();
-      // a group's particles one after the other, a lane per stencil cell
-      {
-        const A* rr = rec + grp * S::GS;
-        const int* rc = s_r + grp * G;
-        const int nw = min(G, cnt - (tid / 64) * 64);   // the wave's first group has the most
-        A acc[NCH];
+      // where runs of one host cell start (the first particle of a group's
+      // share always does); a wave reads its own records only
+      const int prev = __shfl_up(r0, 1);
+      const uint64_t starts_all = __ballot(has && ((lane % S::RP) % PG == 0 || r0 != prev));
 #pragma unroll
-        for (int m = 0; m < NCH; ++m) acc[m] = A(0);
+      for (int rd = 0; rd < S::ROUNDS; ++rd) {
+        const uint64_t starts = S::ROUNDS == 1 ? starts_all : (starts_all >> (rd * S::RP)) & 0xffffffffull;
+        if (starts == 0) continue;   // (wave-uniform: no particle in this round)
+        uint32_t any = 0;   // iterations at which a run starts in some group
+#pragma unroll
+        for (int g = 0; g < S::GROUPS; ++g) any |= (uint32_t)(starts >> (g * PG)) & ((1u << PG) - 1);
+        // the records (a thread without a particle here: zeros, which add nothing)
+        if (S::ROUNDS == 1 || lane / S::RP == rd) {
+          A* rw = rec + (wave * S::WR + lane % S::RP) * S::RS;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) rw[m] = q[m];
+#pragma unroll
+          for (int a = 0; a < 3; ++a) rw[S::W0 + a] = st.w[0][a];
+          if constexpr (F32) {
+#pragma unroll
+            for (int a = 0; a < 9; ++a) rw[S::W1 + a] = st.w[1][a % 3] * st.w[2][NDIM > 2 ? a / 3 : 1];
+          } else {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              rw[S::W1 + a] = st.w[1][a];
+              rw[S::W2 + a] = st.w[2][a];
+            }
+          }
+        }
+        wave_lds_fence();
+        const uint32_t mine = sums_lane ? (uint32_t)(starts >> (grp * PG)) & ((1u << PG) - 1) : 0u;
+        const A* rr = rec + (wave * S::WR + (sums_lane ? grp : 0) * PG) * S::RS;
+        const int* rh = s_r + wave * 64 + rd * S::RP + (sums_lane ? grp : 0) * PG;
+        A acc[NA][NCH];
         int host = -1;
         auto flush = [&]() {
-          if (host >= 0 && s < NT) {
 #pragma unroll
-            for (int m = 0; m < NCH; ++m) atomicAdd(&win[m * WC + host + soff], double(acc[m]));
-          }
+          for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int m = 0; m < NCH; ++m) atomicAdd(&win[m * WC + host + soff + a], double(acc[a][m]));
         };
-        for (int j = 0; j < nw; ++j) {
-          const int r = rc[j];
-          if (r < 0) continue;
-          if (r != host) {
-            flush();
-            host = r;
 #pragma unroll
-            for (int m = 0; m < NCH; ++m) acc[m] = A(0);
-          }
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int m = 0; m < NCH; ++m) acc[a][m] = A(0);
+#pragma unroll 5
+        for (int j = 0; j < PG; ++j) {
           const A* w = rr + j * S::RS;
-          A wt;
-          if constexpr (F32) wt = w[4 + sa] * w[7 + sb + 3 * scc];
-          else wt = w[4 + sa] * (w[7 + sb] * w[10 + (NDIM > 2 ? scc : 1)]);
+          A qj[NCH], wx[NA], wyz;
 #pragma unroll
-          for (int m = 0; m < NCH; ++m) acc[m] += wt * w[m];
+          for (int m = 0; m < NCH; ++m) qj[m] = w[m];
+#pragma unroll
+          for (int a = 0; a < NA; ++a) wx[a] = w[S::W0 + ra + a];
+          if constexpr (F32) wyz = w[S::W1 + rb + 3 * rc];
+          else wyz = w[S::W1 + rb] * w[S::W2 + (NDIM > 2 ? rc : 1)];
+          if ((any >> j) & 1u) {   // (wave-uniform)
+            if ((mine >> j) & 1u) {
+              if (host >= 0) flush();
+              host = rh[j];
+#pragma unroll
+              for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int m = 0; m < NCH; ++m) acc[a][m] = A(0);
+            }
+          }
+#pragma unroll
+          for (int m = 0; m < NCH; ++m) {
+            const A t = wyz * qj[m];
+#pragma unroll
+            for (int a = 0; a < NA; ++a) acc[a][m] += wx[a] * t;
+          }
         }
-        flush();
+        if (host >= 0) flush();
+        if (S::ROUNDS > 1) wave_lds_fence();   // (the next round's records)
       }
-      cur += cnt;
-      if (cnt < SORTED_THREADS) break;   // (uniform) the tile's or the block's last slots
+      done += cnt;
     }
-    __syncthreads();
-    // the window to the grid
-    for (int r = tid; r < WC; r += SORTED_THREADS) {
-      const int a = r % RX, b = (r / RX) % RY, c = r / (RX * RY);
-      if (a >= e0 + 2 || b >= e1 + 2 || (NDIM > 2 && c >= e2 + 2)) continue;
-      const int64_t id = stored_index(B, o0 + a, o1 + b, o2 + c);
-      const double iv = inv_volume(B, o0 + a, o1 + b, o2 + c);
-#pragma unroll
-      for (int m = 0; m < NCH; ++m) {
-        const double x = win[m * WC + r];
-        if (x != 0.0) unsafeAtomicAdd(&fl.dep[m][id], TS(x * iv));
-      }
-    }
-    __syncthreads();
   }
+  __syncthreads();
+  if (kend) window_to_grid();
   if (dg && flags) atomicOr(&dg->flags, (unsigned)flags);
   if constexpr (MODE == SORTED_STEP) {
     if (dg && sums) {
@@ -327,9 +450,126 @@ __global__ void __launch_bounds__(SORTED_THREADS)
   }
 }
 
+// The two half drifts of the unfused step around launch_sorted (SORTED_STEP).
+// In between, a particle's state is one packed record: the sorted pass reads
+// it in an order that has nothing to do with the arrays', and nine arrays
+// would cost it nine lines of memory per particle (5 GB for 4.3 M particles).
+// First drift: arrays to records and sort keys (nbins without a cell; a
+// particle that leaves through an open face loses its cell here).  Second
+// drift: records to arrays.
+template <typename TS, typename A, int GEOM, int NDIM, bool U>
+__global__ void __launch_bounds__(256)
+    k_step_pack(PView<TS> p, const Box* __restrict__ boxes, int nbox, Forces f, A h,
+                const double* __restrict__ tdev, double toff, StepRecord<TS>* __restrict__ rec,
+                uint32_t* __restrict__ key, uint32_t nbins, DiagDev* dg) {
+  constexpr int NC = GEOM == GEOM_CART ? NDIM : 3;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= p.n) return;
+  StepRecord<TS> r{};
+  r.cell = -1;
+  uint32_t k = nbins;
+  int idx[3];
+  A off[3], mom[3];
+  const int b = load_particle<TS, A, GEOM, NDIM>(p, boxes, nbox, i, idx, off, mom, dg);
+  if (b >= 0) {
+    const Box& B = boxes[b];
+    const double t = *tdev + toff;
+    bool alive = drift_any<A, GEOM, NDIM, U>(B, f, true, h, t, idx, off, mom);
+    TS o[3] = {TS(0), TS(0), TS(0)};
+    if (alive)
+      alive = GEOM == GEOM_CART && NDIM == 3 && f.kind == FORCE_FARGO
+                  ? finalize<TS, A, GEOM, NDIM, GEOM == GEOM_CART>(B, f, t, idx, off, mom, o)
+                  : finalize<TS, A, GEOM, NDIM, false>(B, f, t, idx, off, mom, o);
+    if (alive) {
+      r.cell = (int32_t)(B.cell_base + ravel(B, idx));
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        r.off[d] = d < NDIM ? o[d] : TS(0);
+        r.mom[d] = d < NC ? TS(mom[d]) : TS(0);
+      }
+      r.species = p.species ? p.species[i] : 0;
+      r.drag = p.drag ? p.drag[i] : TS(1);
+      r.mass = p.mass ? p.mass[i] : TS(0);
+      k = tile_key_idx(B, idx, TileShape{{sorted_tile_extent(NDIM, 0), sorted_tile_extent(NDIM, 1),
+                                          sorted_tile_extent(NDIM, 2)}});
+    } else {
+      p.cell[i] = -1;
+      if (dg) {
+        atomicAdd(&dg->n_removed, 1ull);
+        atomicOr(&dg->flags, (unsigned)DUST_FLAG_LEFT_OPEN);
+      }
+    }
+  }
+  rec[i] = r;
+  key[i] = k;
+}
+
+template <typename TS, typename A, int GEOM, int NDIM, bool U>
+__global__ void __launch_bounds__(256)
+    k_step_unpack(PView<TS> p, const Box* __restrict__ boxes, int nbox, Forces f, A h,
+                  const double* __restrict__ tdev, double toff, const StepRecord<TS>* __restrict__ rec, DiagDev* dg) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= p.n) return;
+  const StepRecord<TS> r = rec[i];
+  if (r.cell < 0) return;
+  const Box& B = boxes[find_box(boxes, nbox, r.cell)];
+  int idx[3];
+  A off[3], mom[3];
+  unravel(B, r.cell - B.cell_base, idx);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    off[d] = A(r.off[d]);
+    mom[d] = A(r.mom[d]);
+  }
+  const double t = *tdev + toff;
+  const bool alive = drift_any<A, GEOM, NDIM, U>(B, f, false, h, t, idx, off, mom);
+  if (!alive) {
+    // (it keeps the state at the end of the kick)
+    constexpr int NC = GEOM == GEOM_CART ? NDIM : 3;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      if (d < NDIM) p.off[d][i] = r.off[d];
+      if (d < NC) p.mom[d][i] = r.mom[d];
+    }
+  }
+  store_particle_any<TS, A, GEOM, NDIM>(p, B, f, t, i, alive, idx, off, mom, dg);
+}
+
+#define DUST_STEP_SWITCH(KERN, ...)                                                                             \
+  do {                                                                                                          \
+    const dim3 g_((unsigned)((p.n + 255) / 256)), b_(256);                                                      \
+    if (geom == GEOM_CART && ndim == 2 && unif)                                                                 \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_CART, 2, true>), g_, b_, 0, st, __VA_ARGS__);                        \
+    else if (geom == GEOM_CART && ndim == 2)                                                                    \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_CART, 2, false>), g_, b_, 0, st, __VA_ARGS__);                       \
+    else if (geom == GEOM_CART && unif)                                                                         \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_CART, 3, true>), g_, b_, 0, st, __VA_ARGS__);                        \
+    else if (geom == GEOM_CART)                                                                                 \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_CART, 3, false>), g_, b_, 0, st, __VA_ARGS__);                       \
+    else if (geom == GEOM_CYL)                                                                                  \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_CYL, 3, false>), g_, b_, 0, st, __VA_ARGS__);                        \
+    else                                                                                                        \
+      hipLaunchKernelGGL((KERN<TS, A, GEOM_SPH, 3, false>), g_, b_, 0, st, __VA_ARGS__);                        \
+  } while (0)
+
+template <typename TS, typename A>
+void launch_step_pack(const PView<TS>& p, const Box* boxes, int nbox, int geom, int ndim, int unif,
+                      const Forces& f, double h, const double* tdev, double toff, StepRecord<TS>* rec,
+                      uint32_t* key, int64_t nbins, DiagDev* dg, hipStream_t st) {
+  if (p.n == 0) return;
+  DUST_STEP_SWITCH(k_step_pack, p, boxes, nbox, f, A(h), tdev, toff, rec, key, (uint32_t)nbins, dg);
+}
+template <typename TS, typename A>
+void launch_step_unpack(const PView<TS>& p, const Box* boxes, int nbox, int geom, int ndim, int unif,
+                        const Forces& f, double h, const double* tdev, double toff, const StepRecord<TS>* rec,
+                        DiagDev* dg, hipStream_t st) {
+  if (p.n == 0) return;
+  DUST_STEP_SWITCH(k_step_unpack, p, boxes, nbox, f, A(h), tdev, toff, rec, dg);
+}
+
 template <typename TS, typename A, typename TW, int MODE>
 void launch_sorted(const PView<TS>& p, const Box* boxes, int nbox, int geom, int ndim, int unif,
-                   const FView<TS>& fl, const SortedIn<TW>& in, const double* xg, const Forces& f,
+                   const FView<TS>& fl, const SortedIn<TS, TW>& in, const double* xg, const Forces& f,
                    const Species* sp, int drag_mode, double dt, const uint32_t* key, const uint32_t* perm,
                    int64_t nbins, DiagDev* dg, bool sums, hipStream_t st) {
   if (p.n == 0) return;
@@ -353,8 +593,17 @@ void launch_sorted(const PView<TS>& p, const Box* boxes, int nbox, int geom, int
 
 #define DUST_SORTED_INST(TS, A, TW, MODE)                                                                  \
   template void launch_sorted<TS, A, TW, MODE>(                                                            \
-      const PView<TS>&, const Box*, int, int, int, int, const FView<TS>&, const SortedIn<TW>&, const double*, \
+      const PView<TS>&, const Box*, int, int, int, int, const FView<TS>&, const SortedIn<TS, TW>&, const double*, \
       const Forces&, const Species*, int, double, const uint32_t*, const uint32_t*, int64_t, DiagDev*, bool, \
       hipStream_t);
+
+#define DUST_SORTED_STEP_INST(TS, A)                                                                         \
+  DUST_SORTED_INST(TS, A, TS, SORTED_STEP)                                                                   \
+  template void launch_step_pack<TS, A>(const PView<TS>&, const Box*, int, int, int, int, const Forces&,     \
+                                        double, const double*, double, StepRecord<TS>*, uint32_t*, int64_t,  \
+                                        DiagDev*, hipStream_t);                                              \
+  template void launch_step_unpack<TS, A>(const PView<TS>&, const Box*, int, int, int, int, const Forces&,   \
+                                          double, const double*, double, const StepRecord<TS>*, DiagDev*,    \
+                                          hipStream_t);
 
 }  // namespace dust
