@@ -76,10 +76,10 @@ struct Ctx {
   int bin_cur = 0;                // buffer of the last sort's keys / permutation
   size_t bin_bytes = 0;
   void* bin_mem = nullptr;
-  // shadow copy of the particle arrays (binned order) read by the fused step
+  // packed copy of the particles, read by the fused step after a rebinning
   void* shadow_mem = nullptr;
   size_t shadow_cap = 0;          // bytes
-  char* shadow_ptr[12] = {};
+  bool shadow_new = false;        // allocated since the last fused step
   int64_t* bin_start = nullptr;   // nbins+1 (fused path)
   size_t bin_start_cap = 0;
   TileShape tile{{8, 8, 4}};
@@ -394,41 +394,27 @@ void drop_graph(Ctx* c) {
   c->graph_key = GraphKey{};
 }
 
-// Shadow arrays for the particles of p: one per array that p has.
+// Room for the packed copy of the particles of p (ShadowRec, ShadowExt).
 dust_status_t ensure_shadow(Ctx* c, const dust_particles_t* p) {
-  size_t rs = real_size(c), n = (size_t)std::max<int64_t>(p->n, 1);
-  auto rup = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  size_t sizes[12] = {4, rs, rs, rs, rs, rs, rs, rs, rs, 1, 4, 0};
-  size_t need = 0;
-  for (int k = 0; k < 11; ++k) need += rup(n * sizes[k]);
+  const size_t n = (size_t)std::max<int64_t>(p->n, 1), f64 = c->prec == DUST_F64;
+  const size_t need = n * ((f64 ? sizeof(ShadowRec<double>) : sizeof(ShadowRec<float>)) +
+                           (f64 ? sizeof(ShadowExt<double>) : sizeof(ShadowExt<float>)));
   if (need > c->shadow_cap) {
     if (c->shadow_mem) HIP_TRY(hipFree(c->shadow_mem));
     c->shadow_mem = nullptr;
     c->shadow_cap = 0;
     if (hipMalloc(&c->shadow_mem, need) != hipSuccess)
-      return fail(DUST_ENOMEM, "particle shadow arrays of %zu bytes", need);
+      return fail(DUST_ENOMEM, "particle shadow copy of %zu bytes", need);
     c->shadow_cap = need;
-  }
-  char* q = (char*)c->shadow_mem;
-  for (int k = 0; k < 11; ++k) {
-    c->shadow_ptr[k] = q;
-    q += rup(n * sizes[k]);
+    c->shadow_new = true;
   }
   return DUST_OK;
 }
 
-// The shadow arrays as a particle view with the same arrays present as p.
-template <typename TS> PView<TS> shadow_view(Ctx* c, const dust_particles_t* p) {
-  PView<TS> v = pview<TS>(const_cast<dust_particles_t*>(p));
-  v.cell = (int32_t*)c->shadow_ptr[0];
-  for (int d = 0; d < 3; ++d) {
-    v.off[d] = p->off[d] ? (TS*)c->shadow_ptr[1 + d] : nullptr;
-    v.mom[d] = p->mom[d] ? (TS*)c->shadow_ptr[4 + d] : nullptr;
-  }
-  v.drag = p->drag ? (TS*)c->shadow_ptr[7] : nullptr;
-  v.mass = p->mass ? (TS*)c->shadow_ptr[8] : nullptr;
-  v.species = p->species ? (uint8_t*)c->shadow_ptr[9] : nullptr;
-  v.id = p->id ? (int32_t*)c->shadow_ptr[10] : nullptr;
+template <typename TS> ShadowView<TS> shadow_view(Ctx* c, const dust_particles_t* p) {
+  ShadowView<TS> v;
+  v.rec = (ShadowRec<TS>*)c->shadow_mem;
+  v.ext = p->id || p->drag || p->mass ? (ShadowExt<TS>*)(v.rec + std::max<int64_t>(p->n, 1)) : nullptr;
   return v;
 }
 
@@ -671,14 +657,6 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
     launch_feedback<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, st);
 }
 
-// How a fused step moves the particles between the caller's arrays and the
-// context's shadow copy.
-enum StepMove {
-  STEP_IN_PLACE,   // stale bins: x is updated where it is
-  STEP_REBIN,      // new bins: x is sorted into y (level-major slots)
-  STEP_MOVE,       // stale bins, written to y slot for slot
-};
-
 // Whether a fused step runs the FP32 uniform-Cartesian tile kernel
 // (dust_cart3.hip): 3-D Cartesian boxes with uniform axes, FP32 storage and
 // arithmetic, forces none, constant or standard shearing box, masses and
@@ -697,40 +675,38 @@ bool on_layout(const Ctx* c, const PView<float>& p) {
   return c->lay_valid && p.n == c->lay_n && (const void*)p.cell == c->lay_cell;
 }
 
+// One fused step of the particles pv; sh: the packed copy of a rebinning step
+// (the tile kernel reads it in the new order and writes the arrays), else
+// rec null and the particles updated in place.
 template <typename TS, typename A>
-dust_status_t fused_step(Ctx* c, const PView<TS>& x, const PView<TS>& y, const FView<TS>& fv,
-                         const Forces& F, double dt, int flags, StepMove mv, hipStream_t st) {
+dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, const FView<TS>& fv,
+                         const Forces& F, double dt, int flags, hipStream_t st) {
   int nc = ctx_nc(c);
   DiagDev* dg = (flags & DUST_STEP_DIAG) ? c->diag : nullptr;
   constexpr bool f32 = std::is_same<TS, float>::value && std::is_same<A, float>::value;
-  const bool c3 = use_c3(c, f32, F, x);
-  // Rebinning: keys of the cells the particles kick in, a stable sort, and the
-  // source index of every slot in the fused kernel's order, through which
-  // the fused kernel reads x while writing y in binned order (the particles
-  // without a cell are copied across).
-  const uint32_t* src_index = nullptr;
-  if (mv == STEP_REBIN) {
+  const bool c3 = use_c3(c, f32, F, pv);
+  FusedMove<TS> mv{sh, nullptr, nullptr, c->n_active, 0};
+  // Rebinning: keys of the cells the particles kick in and their packed copy,
+  // a stable sort, and the source index of every slot in the fused kernel's
+  // order.
+  if (sh.rec) {
     if constexpr (f32) {
       if (c3)
-        launch_c3_keys(x, c->boxes_d, c->nbox, dt, c->n_active, c->tile, c->bin.key[0], st);
+        launch_c3_keys(pv, c->boxes_d, c->nbox, dt, c->n_active, c->tile, c->bin.key[0], sh, st);
     }
     if (!c3)
-      launch_halfstep_keys<TS, A>(x, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, dt, c->tdev,
-                                  c->n_active, c->tile, c->bin.key[0], st);
-    c->bin_cur = launch_bin(x.cell, x.n, c->boxes_d, c->nbox, c->n_active, DUST_BIN_TILE, c->tile,
+      launch_halfstep_keys<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, dt, c->tdev,
+                                  c->n_active, c->tile, c->bin.key[0], sh, st);
+    c->bin_cur = launch_bin(pv.cell, pv.n, c->boxes_d, c->nbox, c->n_active, DUST_BIN_TILE, c->tile,
                             c->bin, nullptr, c->bin_start, true, st);
     uint32_t* lm = c->bin.val[1 - c->bin_cur];   // free once the sort is done
-    if (c3) {
-      launch_c3_level_perm(c->plan, c->bin.val[c->bin_cur], c->bin_start, lm, st);
-      launch_copy_tail<TS>(x, y, c->bin_start, c->n_active, st, c->bin.val[c->bin_cur]);
-    } else {
-      launch_level_perm<TS>(c->plan, x, y, c->bin.val[c->bin_cur], c->bin_start, c->n_active, lm, st);
-    }
-    src_index = lm;
-  } else if (mv == STEP_MOVE) {
-    launch_copy_tail<TS>(x, y, c->bin_start, c->n_active, st);
+    if (c3) launch_c3_level_perm(c->plan, c->bin.val[c->bin_cur], c->bin_start, lm, st);
+    else launch_level_perm(c->plan, pv.n, c->bin.val[c->bin_cur], c->bin_start, lm, st);
+    mv.src_index = lm;
+    mv.perm = c->bin.val[c->bin_cur];
+    mv.clear_removed = c->shadow_new;
+    c->shadow_new = false;
   }
-  const PView<TS>& out = mv == STEP_IN_PLACE ? x : y;
   if (!(flags & DUST_STEP_NO_FILL))
     launch_fill<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, c->xg, st);
   launch_clear_deposits<TS>(fv, nc + 1, c->n_stored, st);
@@ -739,15 +715,14 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& x, const PView<TS>& y, const F
   hipEvent_t ev1 = prof ? c->prof_ev[2 * c->prof_used + 1] : nullptr;
   if constexpr (f32) {
     if (c3)
-      launch_c3(c->plan, x, out, mv != STEP_IN_PLACE, c->boxes_d, c->nbox, fv, F, c->species_d, c->drag_mode, dt,
+      launch_c3(c->plan, pv, mv, c->boxes_d, c->nbox, fv, F, c->species_d, c->drag_mode, dt,
                 c->tdev, c->bin_start, (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr,
-                src_index, ev0, ev1, st);
+                ev0, ev1, st);
   }
   if (!c3)
-    launch_fused<TS, A>(c->plan, x, out, mv != STEP_IN_PLACE, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif,
+    launch_fused<TS, A>(c->plan, pv, mv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif,
                         fv, F, c->species_d, c->drag_mode, dt, c->tdev, c->bin_start,
-                        (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr, src_index,
-                        ev0, ev1, st);
+                        (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr, ev0, ev1, st);
   HIP_TRY(hipGetLastError());
   if (prof) ++c->prof_used;
   if (dg)
@@ -774,27 +749,12 @@ dust_status_t run_steps(Ctx* c, dust_particles_t* p, dust_fields_t* f, double dt
     }
     return DUST_OK;
   }
-  // Every rebinning moves the particles to the other buffer (the caller's
-  // arrays or the shadow copy).  With an odd number of rebinnings the last
-  // step with stale bins is done out of place instead, so that the call ends
-  // in the caller's arrays; with none, a copy at the end.
-  PView<TS> sh = shadow_view<TS>(c, p);
-  int nrebin = (nsteps + rebin_every - 1) / rebin_every;
-  int last_stale = -1;
-  for (int s = 0; s < nsteps; ++s)
-    if (s % rebin_every) last_stale = s;
-  const bool odd = nrebin % 2 == 1;
-  bool in_shadow = false;
+  const ShadowView<TS> sh = shadow_view<TS>(c, p), none{nullptr, nullptr};
   for (int s = 0; s < nsteps; ++s) {
-    StepMove mv = s % rebin_every == 0 ? STEP_REBIN : (odd && s == last_stale) ? STEP_MOVE : STEP_IN_PLACE;
-    const PView<TS>& x = in_shadow ? sh : pv;
-    const PView<TS>& y = in_shadow ? pv : sh;
-    dust_status_t e = fused_step<TS, A>(c, x, y, fv, F, dt, flags, mv, st);
+    dust_status_t e = fused_step<TS, A>(c, pv, s % rebin_every == 0 ? sh : none, fv, F, dt, flags, st);
     if (e) return e;
-    if (mv != STEP_IN_PLACE) in_shadow = !in_shadow;
     launch_advance_time(c->tdev, dt, (flags & DUST_STEP_DIAG) ? c->diag : nullptr, st);
   }
-  if (in_shadow) launch_copy_particles<TS>(sh, pv, st);
   constexpr bool f32 = std::is_same<TS, float>::value && std::is_same<A, float>::value;
   c->lay_valid = use_c3(c, f32, F, pv);
   c->lay_n = pv.n;

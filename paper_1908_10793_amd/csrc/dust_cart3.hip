@@ -80,10 +80,11 @@ __global__ void __launch_bounds__(256)
 }
 
 // Half-step tile keys with the drift of the fast path (a particle is then
-// normally processed by the thread of the cell it kicks in).
+// normally processed by the thread of the cell it kicks in), and the
+// particles packed for the tile kernel, which reads them in sorted order.
 __global__ void __launch_bounds__(256)
     k_c3_keys(PView<float> p, const Box* __restrict__ boxes, int nbox, float dt,
-              uint32_t nbins, TileShape ts, uint32_t* __restrict__ key) {
+              uint32_t nbins, TileShape ts, uint32_t* __restrict__ key, ShadowView<float> sh) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= p.n) return;
   const int32_t c = p.cell[i];
@@ -93,6 +94,7 @@ __global__ void __launch_bounds__(256)
     off[d] = p.off[d][i];
     mom[d] = p.mom[d][i];
   }
+  pack_particle(p, i, c, off, mom, sh);
   uint32_t k = nbins;
   if (c >= 0 && c < (int32_t)nbins) {
     const Box& B = nbox == 1 ? boxes[0] : boxes[find_box(boxes, nbox, c)];
@@ -119,16 +121,14 @@ size_t c3_lds_bytes(const FusedPlan& plan) {
   return (size_t)plan.lds_cells * (4 * sizeof(double) + sizeof(float4));
 }
 
-void launch_c3(const FusedPlan& plan, const PView<float>& p, const PView<float>& q, bool copy_attrs,
+void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv,
                const Box* boxes_d, int nbox, const FView<float>& fl, const Forces& f, const Species* sp,
                int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
-               DiagDev* dg, bool sums, const uint32_t* src_index, hipEvent_t ev0, hipEvent_t ev1,
-               hipStream_t st) {
+               DiagDev* dg, bool sums, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   if (plan.ntiles == 0) return;
   if (ev0) (void)hipEventRecord(ev0, st);
 #define DUST_C3(TX, TY, TZ)                                                                             \
-  launch_c3_shape<TX, TY, TZ>(plan, p, q, copy_attrs, boxes_d, fl, f, sp, drag_mode, dt, tdev, bin_start,  \
-                              xg, dg, sums, src_index, st)
+  launch_c3_shape<TX, TY, TZ>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st)
   switch (plan.shape) {
     case 0: DUST_C3(8, 8, 4); break;
     case 1: DUST_C3(16, 4, 4); break;
@@ -140,10 +140,10 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const PView<float>&
 #undef DUST_C3
   if (ev1) (void)hipEventRecord(ev1, st);
   hipLaunchKernelGGL((k_fused_deferred<float, float, GEOM_CART, 3, true>), dim3(DEFER_BLOCKS), dim3(256), 0, st,
-                     p, q, (int)copy_attrs, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
+                     p, mv.sh, mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
                      (const uint32_t*)plan.defer_list, (const uint32_t*)plan.defer_count, plan.part_d,
                      plan.ntiles, (int)sums, dg);
-  launch_reduce_fused(plan, dg, sums, st);
+  launch_reduce_fused<float>(plan, dg, sums, p, mv, bin_start, st);
 }
 
 void launch_c3_aux(const FusedPlan& plan, const PView<float>& p, const Box* boxes_d, int nbox,
@@ -164,10 +164,10 @@ void launch_c3_aux(const FusedPlan& plan, const PView<float>& p, const Box* boxe
 }
 
 void launch_c3_keys(const PView<float>& p, const Box* boxes_d, int nbox, double dt, int64_t nbins,
-                    TileShape ts, uint32_t* key, hipStream_t st) {
+                    TileShape ts, uint32_t* key, const ShadowView<float>& sh, hipStream_t st) {
   if (p.n == 0) return;
   hipLaunchKernelGGL(k_c3_keys, dim3((unsigned)((p.n + 255) / 256)), dim3(256), 0, st, p, boxes_d, nbox,
-                     float(dt), (uint32_t)nbins, ts, key);
+                     float(dt), (uint32_t)nbins, ts, key, sh);
 }
 
 void launch_c3_level_perm(const FusedPlan& plan, const uint32_t* perm, const int64_t* bin_start,

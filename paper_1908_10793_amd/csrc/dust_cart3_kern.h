@@ -185,7 +185,7 @@ struct C3Raw {
   float off[3], mom[3];
 };
 
-// ID: also the id (when the attributes are copied to another buffer).
+// From the arrays.  ID: also the id.
 template <bool ID>
 __device__ __forceinline__ void c3_load(const PView<float>& p, uint32_t i, C3Raw& r) {
   r.cell = at32(p.cell, i);
@@ -201,6 +201,23 @@ __device__ __forceinline__ void c3_load(const PView<float>& p, uint32_t i, C3Raw
   }
   r.species = (int32_t)at32(p.species ? p.species : reinterpret_cast<const uint8_t*>(p.cell),
                             p.species ? i : 0u);
+}
+
+// From the packed copy of a rebinning: two 16-byte loads of one 32-byte
+// place, where the seven arrays were seven scattered loads (the id, where
+// there is one, from the attributes' record, else ignored).
+__device__ __forceinline__ void c3_load(const ShadowView<float>& sh, uint32_t i, C3Raw& r) {
+  const float4* q = reinterpret_cast<const float4*>(sh.rec) + 2 * (size_t)i;
+  const float4 a = q[0], b = q[1];
+  r.cell = __float_as_int(a.x);
+  r.species = __float_as_int(a.y);
+  r.off[0] = a.z;
+  r.off[1] = a.w;
+  r.off[2] = b.x;
+  r.mom[0] = b.y;
+  r.mom[1] = b.z;
+  r.mom[2] = b.w;
+  r.id = sh.ext ? sh.ext[i].id : 0;
 }
 
 // The stencil planes of a particle one cell off its thread's cell (shift
@@ -242,15 +259,16 @@ __device__ __forceinline__ void c3_spill_planes(double* dep, int base, int sx, i
 }
 
 // The fused step.  SB: standard shearing-box forces (else none or a constant
-// acceleration).  SMALL: every box of the launch has fewer than 2^24 cells.  REBIN: the step after a rebinning (particles read through
-// src_index, attributes copied, input checks); else COPY: stale bins written
-// to another buffer slot for slot (attributes copied), or in place.  Masses
-// and stopping times come from the species table.
-template <int TX, int TY, int TZ, bool SB, bool REBIN, bool COPY, bool SMALL>
+// acceleration).  SMALL: every box of the launch has fewer than 2^24 cells.  
+// REBIN: the step after a rebinning (the packed particles read through
+// src_index and written to the arrays in binned order, attributes too, with
+// input checks); else stale bins, in place.  Masses and stopping times come
+// from the species table.
+template <int TX, int TY, int TZ, bool SB, bool REBIN, bool SMALL>
 __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
     k_c3(const TileDesc* __restrict__ tiles, const uint8_t* __restrict__ tmap, PView<float> p,
-         PView<float> dst, int copy_attrs, const Box* __restrict__ boxes, FView<float> fl, Forces f,
-         const Species* __restrict__ sp, int drag_mode, float dt, const double* __restrict__ tdev,
+         ShadowView<float> sh, const Box* __restrict__ boxes, FView<float> fl, Forces f,
+         const Species* __restrict__ sp, float dt, const double* __restrict__ tdev,
          const int64_t* __restrict__ bin_start, const double* __restrict__ xg, DiagDev* dg,
          double* __restrict__ part, int sums, uint32_t* __restrict__ defer_list,
          uint32_t* __restrict__ defer_count, const uint32_t* __restrict__ src_index) {
@@ -274,9 +292,8 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
   constexpr int NW = FUSED_THREADS / 64;
   __shared__ int spq_r[NW][64], spq_s[NW][64];
   __shared__ float spq_o[NW][3][64], spq_q[NW][4][64];
-  // where the particles are written: stale bins in place write the arrays
-  // they read (the same pointers, held once)
-  const PView<float>& out = COPY ? dst : p;
+  constexpr bool COPY = REBIN;   // attributes are written too
+  const PView<float>& out = p;
   const TileDesc td = tiles[blockIdx.x];
   const Box& B = boxes[td.box];
   const C3Box cb = c3_box(B, dt);
@@ -407,8 +424,10 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
     if constexpr (REBIN) {
       nxt_si = at32(src_index, nxt_si);
       si_b = at32(src_index, si_b);
+      c3_load(sh, nxt_si, nxt);
+    } else {
+      c3_load<false>(p, nxt_si, nxt);
     }
-    c3_load<COPY>(p, nxt_si, nxt);
     // wait for the first particle here (once per thread): otherwise the wait
     // analysis at the loop head, which merges this entry with the back edge,
     // keeps these loads pending there and waits, behind every store of the
@@ -445,7 +464,6 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
   for (int j = 0; j < nlev; ++j) {
     const bool has = wl.cnt > j;
     const uint32_t i = slot;
-    const uint32_t si = nxt_si;
     const C3Raw cur = nxt;
     store_pending();
     slot = slot_b;
@@ -454,7 +472,8 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
     // issued at the last level too (the wave's first slot then, in range;
     // the values go unused): with no skipped load, the prefetch registers
     // need no copy of their old values on every iteration
-    c3_load<COPY>(p, nxt_si, nxt);
+    if constexpr (REBIN) c3_load(sh, nxt_si, nxt);
+    else c3_load<false>(p, nxt_si, nxt);
     si_b = valid(j + 2, slot_b);
     if constexpr (REBIN) {
       if (j + 2 < nlev) si_b = at32(src_index, si_b);
@@ -547,8 +566,7 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
         if (lane == leader) base = atomicAdd(defer_count, (uint32_t)__popcll(dm));
         base = __shfl(base, leader, 64);
         if (deferred) {
-          defer_list[2 * (base + lanes_below(dm))] = i;
-          defer_list[2 * (base + lanes_below(dm)) + 1] = si;
+          defer_list[base + lanes_below(dm)] = i;
         }
       }
     }
@@ -823,13 +841,12 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
   }
 }
 
-template <int TX, int TY, int TZ, bool SB, bool REBIN, bool COPY, bool SMALL>
-void launch_c3_t(const FusedPlan& plan, const PView<float>& p, const PView<float>& q, const Box* boxes_d,
-                 const FView<float>& fl, const Forces& f, const Species* sp, int drag_mode, double dt,
-                 const double* tdev, const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums,
-                 const uint32_t* src_index, hipStream_t st) {
+template <int TX, int TY, int TZ, bool SB, bool REBIN, bool SMALL>
+void launch_c3_t(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv, const Box* boxes_d,
+                 const FView<float>& fl, const Forces& f, const Species* sp, double dt, const double* tdev,
+                 const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, hipStream_t st) {
   const size_t lds = c3_lds_bytes(plan);
-  auto kern = k_c3<TX, TY, TZ, SB, REBIN, COPY, SMALL>;
+  auto kern = k_c3<TX, TY, TZ, SB, REBIN, SMALL>;
   if (lds > 64 * 1024) {
     static bool raised = false;
     if (!raised) {
@@ -838,47 +855,42 @@ void launch_c3_t(const FusedPlan& plan, const PView<float>& p, const PView<float
       raised = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(FUSED_THREADS), lds, st, plan.tiles_d, plan.tile_map, p, q,
-                     COPY ? 1 : 0, boxes_d, fl, f, sp, drag_mode, float(dt), tdev, bin_start, xg, dg,
-                     plan.part_d, (int)sums, plan.defer_list, plan.defer_count, src_index);
+  hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(FUSED_THREADS), lds, st, plan.tiles_d, plan.tile_map, p, mv.sh,
+                     boxes_d, fl, f, sp, float(dt), tdev, bin_start, xg, dg, plan.part_d, (int)sums,
+                     plan.defer_list, plan.defer_count, mv.src_index);
 }
 
 // The tile kernel of one tile shape: forces (standard shearing box or not)
-// and the kind of step (after a rebinning through src_index; stale bins
-// written across with copy_attrs; stale bins in place).
+// and the kind of step (after a rebinning, or stale bins in place).
 template <int TX, int TY, int TZ>
-void launch_c3_shape(const FusedPlan& plan, const PView<float>& p, const PView<float>& q, bool copy_attrs,
-                     const Box* boxes_d, const FView<float>& fl, const Forces& f, const Species* sp,
-                     int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
-                     DiagDev* dg, bool sums, const uint32_t* src_index, hipStream_t st) {
-#define DUST_C3M(SBV, RB, CP)                                                                               \
-  do {                                                                                                      \
-    if (plan.small)                                                                                         \
-      launch_c3_t<TX, TY, TZ, SBV, RB, CP, true>(plan, p, q, boxes_d, fl, f, sp, drag_mode, dt, tdev,       \
-                                                 bin_start, xg, dg, sums, src_index, st);                   \
-    else                                                                                                    \
-      launch_c3_t<TX, TY, TZ, SBV, RB, CP, false>(plan, p, q, boxes_d, fl, f, sp, drag_mode, dt, tdev,      \
-                                                  bin_start, xg, dg, sums, src_index, st);                  \
+void launch_c3_shape(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv, const Box* boxes_d,
+                     const FView<float>& fl, const Forces& f, const Species* sp, double dt, const double* tdev,
+                     const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, hipStream_t st) {
+#define DUST_C3M(SBV, RB)                                                                                      \
+  do {                                                                                                         \
+    if (plan.small)                                                                                            \
+      launch_c3_t<TX, TY, TZ, SBV, RB, true>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,     \
+                                             sums, st);                                                        \
+    else                                                                                                       \
+      launch_c3_t<TX, TY, TZ, SBV, RB, false>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,    \
+                                              sums, st);                                                       \
   } while (0)
   const bool sb = f.kind == FORCE_SHEARBOX;
-  if (src_index) {
-    if (sb) DUST_C3M(true, true, true);
-    else DUST_C3M(false, true, true);
-  } else if (copy_attrs) {
-    if (sb) DUST_C3M(true, false, true);
-    else DUST_C3M(false, false, true);
+  if (mv.sh.rec) {
+    if (sb) DUST_C3M(true, true);
+    else DUST_C3M(false, true);
   } else {
-    if (sb) DUST_C3M(true, false, false);
-    else DUST_C3M(false, false, false);
+    if (sb) DUST_C3M(true, false);
+    else DUST_C3M(false, false);
   }
 #undef DUST_C3M
 }
 
 #define DUST_C3_SHAPE_DECL(PREFIX, TX, TY, TZ)                                                              \
   PREFIX template void launch_c3_shape<TX, TY, TZ>(                                                         \
-      const FusedPlan&, const PView<float>&, const PView<float>&, bool, const Box*, const FView<float>&,     \
-      const Forces&, const Species*, int, double, const double*, const int64_t*, const double*, DiagDev*,   \
-      bool, const uint32_t*, hipStream_t);
+      const FusedPlan&, const PView<float>&, const FusedMove<float>&, const Box*, const FView<float>&,       \
+      const Forces&, const Species*, double, const double*, const int64_t*, const double*, DiagDev*, bool,   \
+      hipStream_t);
 #define DUST_C3_SHAPES(PREFIX)                                                                              \
   DUST_C3_SHAPE_DECL(PREFIX, 8, 8, 4)                                                                       \
   DUST_C3_SHAPE_DECL(PREFIX, 16, 4, 4)                                                                      \

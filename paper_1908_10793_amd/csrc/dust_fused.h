@@ -29,10 +29,28 @@ struct FusedPlan {
   TileDesc* tiles_d = nullptr;
   double* part_d = nullptr;   // per-tile diagnostic partials (+ the deferred kernel's)
   uint32_t* defer_count = nullptr;   // deferred particles of the current launch
-  uint32_t* defer_list = nullptr;    // their (slot, source) pairs (capacity defer_cap pairs)
+  uint32_t* defer_list = nullptr;    // their slots (capacity defer_cap)
   size_t defer_cap = 0;
   uint8_t* tile_map = nullptr;       // per tile, 256 tile-local cells in thread order (FP32
                                      // Cartesian path: ranked by particle count at each rebinning)
+};
+
+// A particle's state as a rebinning packs it (the shadow copy of the fused
+// step): one place to read per particle for the tile kernel, which takes them
+// in sorted order.  Ext: the attributes that not every run has.
+template <typename TS> struct __attribute__((aligned(16))) ShadowRec {
+  int32_t cell, species;
+  TS off[3], mom[3];
+};
+template <typename TS> struct __attribute__((aligned(16))) ShadowExt {
+  int32_t id;
+  TS drag, mass;
+};
+static_assert(sizeof(ShadowRec<float>) == 32 && sizeof(ShadowExt<float>) == 16, "FP32 records");
+static_assert(sizeof(ShadowRec<double>) == 64 && sizeof(ShadowExt<double>) == 32, "FP64 records");
+template <typename TS> struct ShadowView {
+  ShadowRec<TS>* rec;   // null: no rebinning in this step
+  ShadowExt<TS>* ext;   // null where the particles have no id, drag and mass
 };
 
 // Capacity of the deferred-particle list for n particles.
@@ -45,61 +63,64 @@ void fused_plan_free(FusedPlan& plan);
 size_t fused_lds_bytes(const FusedPlan& plan, int nc, int ts_bytes);
 static constexpr size_t FUSED_STATIC_LDS = 5 * 256 * sizeof(double) + 3 * DUST_MAX_SPECIES * sizeof(double) + 256;
 
-// One fused step over every tile (binned by tile-major key, bin_start):
-// slot s of q receives the update of particle src_index[s] of p, or of
-// particle s when src_index is null (then q may be p: in place); copy_attrs
-// copies drag / mass / species / id along.  xg: the context's FP64 x-ghost
+// One fused step over every tile (binned by tile-major key, bin_start).
+// After a rebinning (sh.rec given): slot s of p receives the update of the
+// packed particle src_index[s], attributes too, and the slots from
+// bin_start[nbins] on (no tile visits them) the packed particles perm[s];
+// else the particles of p are updated in place.  clear_removed: a particle
+// that leaves in the second half drift of a rebinning step keeps whatever its
+// new slot held; this zeroes that instead.  xg: the context's FP64 x-ghost
 // gas layers (filled this step), or null.  ev0 / ev1 (nullable) are recorded
 // around the tile kernel alone (not the deferred-particle kernel).
+template <typename TS> struct FusedMove {
+  ShadowView<TS> sh;
+  const uint32_t* src_index;
+  const uint32_t* perm;
+  int64_t nbins;
+  int clear_removed;
+};
 template <typename TS, typename A>
-void launch_fused(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& q, bool copy_attrs,
+void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv,
                   const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
                   const Forces& f, const Species* sp, int drag_mode, double dt, const double* tdev,
                   const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums,
-                  const uint32_t* src_index, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
+                  hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
 
-// Keys (tile-major) of the cells the particles reach in the first half drift
-// of a step of length dt starting at *tdev.
+// A rebinning's first pass: keys (tile-major) of the cells the particles
+// reach in the first half drift of a step of length dt starting at *tdev, and
+// the particles packed into sh.
 template <typename TS, typename A>
 void launch_halfstep_keys(const PView<TS>& p, const Box* boxes_d, int nbox, int geom, int ndim,
                           int unif, const Forces& f, double dt, const double* tdev, int64_t nbins,
-                          TileShape ts, uint32_t* key, hipStream_t st);
+                          TileShape ts, uint32_t* key, const ShadowView<TS>& sh, hipStream_t st);
 
-// After a sort of src (perm, bin_start): lm = the source index of every
-// binned slot in the fused kernel's level-major layout within each wave's
-// range of slots; the particles without a cell (sorted slots from
-// bin_start[nbins] on, which no tile visits) are copied to the same slots of
-// dst (distinct from src).
-template <typename TS>
-void launch_level_perm(const FusedPlan& plan, const PView<TS>& src, const PView<TS>& dst,
-                       const uint32_t* perm, const int64_t* bin_start, int64_t nbins, uint32_t* lm,
-                       hipStream_t st);
-
-// The particles without a cell (slots from bin_start[nbins] on): dst[s] =
-// src[perm[s]], or src[s] when perm is null (distinct arrays).
-template <typename TS>
-void launch_copy_tail(const PView<TS>& src, const PView<TS>& dst, const int64_t* bin_start, int64_t nbins,
-                      hipStream_t st, const uint32_t* perm = nullptr);
+// After the sort (perm, bin_start): lm = the source index of every binned
+// slot in the fused kernel's level-major layout within each wave's range of
+// slots.
+void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, const int64_t* bin_start,
+                       uint32_t* lm, hipStream_t st);
 
 // Adds the per-workgroup diagnostic partials of the last fused launch (tile
 // kernel and deferred kernel) to the diagnostics block, and resets the
-// deferred-particle count.
-void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, hipStream_t st);
+// deferred-particle count; after a rebinning also fills the slots without a
+// cell (see launch_fused).
+template <typename TS>
+void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, const PView<TS>& p,
+                         const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st);
 
 // The fused step of uniform 3-D Cartesian boxes in FP32 storage and
 // arithmetic (dust_cart3.hip), with forces none, constant or standard
 // shearing box: the tile kernel (ev0 / ev1 around it), the deferred-particle
 // kernel and the reduction of their diagnostic partials.
-void launch_c3(const FusedPlan& plan, const PView<float>& p, const PView<float>& q, bool copy_attrs,
+void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv,
                const Box* boxes_d, int nbox, const FView<float>& fl, const Forces& f, const Species* sp,
                int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
-               DiagDev* dg, bool sums, const uint32_t* src_index, hipEvent_t ev0, hipEvent_t ev1,
-               hipStream_t st);
-// Its rebinning: half-step tile keys with its own drift, and after the sort
-// the per-tile ranking of cells by count (plan.tile_map) with the source
-// index of every slot (lm).
+               DiagDev* dg, bool sums, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
+// Its rebinning: half-step tile keys with its own drift (and the packed
+// particles), and after the sort the per-tile ranking of cells by count
+// (plan.tile_map) with the source index of every slot (lm).
 void launch_c3_keys(const PView<float>& p, const Box* boxes_d, int nbox, double dt, int64_t nbins,
-                    TileShape ts, uint32_t* key, hipStream_t st);
+                    TileShape ts, uint32_t* key, const ShadowView<float>& sh, hipStream_t st);
 void launch_c3_level_perm(const FusedPlan& plan, const uint32_t* perm, const int64_t* bin_start, uint32_t* lm,
                           hipStream_t st);
 // Predictor drag source (mass: dust density) on the binned layout of the
@@ -109,10 +130,5 @@ void launch_c3_aux(const FusedPlan& plan, const PView<float>& p, const Box* boxe
                    const FView<float>& fl, float* const out[3], bool mass, const Forces& f, const Species* sp,
                    double dt, const int64_t* bin_start, int64_t nbins, DiagDev* dg, hipStream_t st);
 size_t c3_lds_bytes(const FusedPlan& plan);
-
-// dst = src, every particle array.
-template <typename TS>
-void launch_copy_particles(const PView<TS>& src, const PView<TS>& dst, hipStream_t st);
-
 
 }  // namespace dust

@@ -1,6 +1,6 @@
 // Fused tile step: plan (tile table), the dispatcher over geometries and the
-// partial reduction, and the rebinning kernels (half-step keys, level-major
-// permutation, particle copies).  The kernels themselves are in
+// partial reduction, and the rebinning kernels (half-step keys and packing,
+// level-major permutation).  The kernels themselves are in
 // dust_fused_kern.h.
 #include <algorithm>
 #include <vector>
@@ -109,8 +109,7 @@ dust_status_t fused_plan_reserve(FusedPlan& plan, int64_t n) {
   plan.defer_list = nullptr;
   plan.defer_cap = 0;
   size_t cap = (size_t)std::max<int64_t>(n, 1);
-  // (slot written, particle read) pairs
-  if (hipMalloc((void**)&plan.defer_list, 2 * cap * sizeof(uint32_t)) != hipSuccess) return DUST_ENOMEM;
+  if (hipMalloc((void**)&plan.defer_list, cap * sizeof(uint32_t)) != hipSuccess) return DUST_ENOMEM;
   plan.defer_cap = cap;
   return DUST_OK;
 }
@@ -120,11 +119,22 @@ size_t fused_lds_bytes(const FusedPlan& plan, int nc, int ts_bytes) {
 }
 
 // Adds the per-workgroup partials of one fused launch to the diagnostics
-// block, in a fixed order (one workgroup).
+// block, in a fixed order (one workgroup).  After a rebinning further
+// workgroups put the packed particles without a cell in the slots from
+// bin_start[nbins] on, which no tile visits (it is usually none).
 static constexpr int REDUCE_THREADS = 1024;
+static constexpr int REDUCE_TAIL_BLOCKS = 31;
+template <typename TS>
 __global__ void __launch_bounds__(REDUCE_THREADS)
     k_reduce_fused_partials(const double* __restrict__ part, int n, DiagDev* dg, int sums,
-                            uint32_t* defer_count) {
+                            uint32_t* defer_count, PView<TS> p, FusedMove<TS> mv,
+                            const int64_t* __restrict__ bin_start) {
+  if (blockIdx.x > 0) {
+    for (int64_t s = bin_start[mv.nbins] + (int64_t)(blockIdx.x - 1) * REDUCE_THREADS + threadIdx.x; s < p.n;
+         s += (int64_t)REDUCE_TAIL_BLOCKS * REDUCE_THREADS)
+      unpack_particle(mv.sh, mv.perm[s], p, s);
+    return;
+  }
   constexpr int NW = REDUCE_THREADS / 64;
   static_assert(REDUCE_THREADS % PART_WORDS == 0 && 64 % PART_WORDS == 0, "word per lane");
   __shared__ double wred[NW][PART_WORDS];
@@ -176,19 +186,18 @@ DUST_FUSED_G_ALL(extern, float, float)
 DUST_FUSED_G_ALL(extern, double, double)
 
 template <typename TS, typename A>
-void launch_fused(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& q, bool copy_attrs,
-                  const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
+void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
                   const Forces& f, const Species* sp, int drag_mode, double dt, const double* tdev,
                   const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums,
-                  const uint32_t* src_index, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
+                  hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   if (plan.ntiles == 0) return;
   double* part = plan.part_d;
   // (the deferred-particle count is zero here: set at set-up, and reset by
   // the partial reduction that ends every launch)
 #define DUST_G(G, D, UU)                                                                          \
-  launch_fused_g<TS, A, G, D, UU>(plan, p, q, copy_attrs, boxes_d, fl, f, sp, drag_mode, dt, tdev, \
+  launch_fused_g<TS, A, G, D, UU>(plan, p, mv, boxes_d, fl, f, sp, drag_mode, dt, tdev,            \
                                   bin_start, xg, dg, part, sums, plan.defer_list,                  \
-                                  plan.defer_count, src_index, nbox, ev0, ev1, st)
+                                  plan.defer_count, nbox, ev0, ev1, st)
   if (geom == GEOM_CART && ndim == 2 && unif) DUST_G(GEOM_CART, 2, true);
   else if (geom == GEOM_CART && ndim == 2) DUST_G(GEOM_CART, 2, false);
   else if (geom == GEOM_CART && unif) DUST_G(GEOM_CART, 3, true);
@@ -196,13 +205,16 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& q,
   else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
   else DUST_G(GEOM_SPH, 3, false);
 #undef DUST_G
-  launch_reduce_fused(plan, dg, sums, st);
+  launch_reduce_fused<TS>(plan, dg, sums, p, mv, bin_start, st);
 }
 
-void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, hipStream_t st) {
+template <typename TS>
+void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, const PView<TS>& p,
+                         const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st) {
   if (plan.ntiles == 0) return;
-  hipLaunchKernelGGL(k_reduce_fused_partials, dim3(1), dim3(REDUCE_THREADS), 0, st, (const double*)plan.part_d,
-                     plan.ntiles + DEFER_BLOCKS, dg, (int)sums, plan.defer_count);
+  hipLaunchKernelGGL((k_reduce_fused_partials<TS>), dim3(mv.sh.rec ? 1 + REDUCE_TAIL_BLOCKS : 1),
+                     dim3(REDUCE_THREADS), 0, st, (const double*)plan.part_d, plan.ntiles + DEFER_BLOCKS, dg,
+                     (int)sums, plan.defer_count, p, mv, bin_start);
 }
 
 // ---------------------------------------------------------------- rebinning by half-step cell
@@ -212,12 +224,17 @@ void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, hipStrea
 // by the thread of the cell it kicks in).  A particle that leaves through an
 // open face keeps the key of its current cell (the fused kernel removes it);
 // a particle without a valid cell gets key nbins.  (The sort takes the
-// particle indices as values.)
+// particle indices as values.)  The particles are packed into sh on the way:
+// the tile kernel, at its 2 waves per SIMD, reads them in sorted order, where
+// seven to nine arrays cost it as many scattered reads each.  (A separate
+// pass that moved the arrays into sorted order, at 7 waves per SIMD, took
+// longer than the packing and the kernel's own reads: 8.7 ms for 120 M
+// particles.)
 template <typename TS, typename A, int GEOM, int NDIM, bool U>
 __global__ void __launch_bounds__(256)
     k_halfstep_keys(PView<TS> p, const Box* __restrict__ boxes, int nbox, Forces f, A dt,
                     const double* __restrict__ tdev, uint32_t nbins, TileShape ts,
-                    uint32_t* __restrict__ key) {
+                    uint32_t* __restrict__ key, ShadowView<TS> sh) {
   constexpr int nc = GEOM == GEOM_CART ? NDIM : 3;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= p.n) return;
@@ -229,6 +246,7 @@ __global__ void __launch_bounds__(256)
     off[d] = d < NDIM ? A(p.off[d][i]) : A(0);
     mom[d] = d < nc ? A(p.mom[d][i]) : A(0);
   }
+  pack_particle(p, i, c, off, mom, sh);
   uint32_t k = nbins;
   auto key_in = [&](const Box& B) {
     int idx[3];
@@ -253,12 +271,12 @@ __global__ void __launch_bounds__(256)
 template <typename TS, typename A>
 void launch_halfstep_keys(const PView<TS>& p, const Box* boxes_d, int nbox, int geom, int ndim,
                           int unif, const Forces& f, double dt, const double* tdev, int64_t nbins,
-                          TileShape ts, uint32_t* key, hipStream_t st) {
+                          TileShape ts, uint32_t* key, const ShadowView<TS>& sh, hipStream_t st) {
   if (p.n == 0) return;
   unsigned g = (unsigned)((p.n + 255) / 256);
 #define DUST_K(G, D, UU)                                                                          \
   hipLaunchKernelGGL((k_halfstep_keys<TS, A, G, D, UU>), dim3(g), dim3(256), 0, st, p, boxes_d,     \
-                     nbox, f, A(dt), tdev, (uint32_t)nbins, ts, key)
+                     nbox, f, A(dt), tdev, (uint32_t)nbins, ts, key, sh)
   if (geom == GEOM_CART && ndim == 2 && unif) DUST_K(GEOM_CART, 2, true);
   else if (geom == GEOM_CART && ndim == 2) DUST_K(GEOM_CART, 2, false);
   else if (geom == GEOM_CART && unif) DUST_K(GEOM_CART, 3, true);
@@ -266,22 +284,6 @@ void launch_halfstep_keys(const PView<TS>& p, const Box* boxes_d, int nbox, int 
   else if (geom == GEOM_CYL) DUST_K(GEOM_CYL, 3, false);
   else DUST_K(GEOM_SPH, 3, false);
 #undef DUST_K
-}
-
-// Copy particle `from` of src to slot `to` of dst (every array src has).
-template <typename TS>
-__device__ __forceinline__ void copy_particle(const PView<TS>& src, int64_t from, const PView<TS>& dst,
-                                              int64_t to) {
-  dst.cell[to] = src.cell[from];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    if (src.off[d]) dst.off[d][to] = src.off[d][from];
-    if (src.mom[d]) dst.mom[d][to] = src.mom[d][from];
-  }
-  if (src.drag) dst.drag[to] = src.drag[from];
-  if (src.mass) dst.mass[to] = src.mass[from];
-  if (src.species) dst.species[to] = src.species[from];
-  if (src.id) dst.id[to] = src.id[from];
 }
 
 // The level-major order of each tile's binned particles as a permutation:
@@ -309,80 +311,29 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Particles without a cell (sorted last, from slot bin_start[nbins] on), which
-// no tile visits: dst[s] = src[perm[s]], or src[s] when perm is null (src and
-// dst distinct).
-template <typename TS>
-__global__ void __launch_bounds__(256)
-    k_copy_tail(PView<TS> src, PView<TS> dst, const uint32_t* __restrict__ perm,
-                const int64_t* __restrict__ bin_start, int64_t nbins) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t s = bin_start[nbins] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < src.n;
-       s += stride)
-    copy_particle(src, perm ? (int64_t)perm[s] : s, dst, s);
-}
-
-// dst = src, every array.
-template <typename TS>
-__global__ void __launch_bounds__(256) k_copy_particles(PView<TS> src, PView<TS> dst) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < src.n; s += stride)
-    copy_particle(src, s, dst, s);
-}
-
-template <typename TS>
-void launch_level_perm(const FusedPlan& plan, const PView<TS>& src, const PView<TS>& dst,
-                       const uint32_t* perm, const int64_t* bin_start, int64_t nbins, uint32_t* lm,
-                       hipStream_t st) {
-  if (src.n == 0) return;
-  if (plan.ntiles > 0)
-    hipLaunchKernelGGL(k_level_perm, dim3(plan.ntiles), dim3(256), 0, st, plan.tiles_d, plan.tile, perm,
-                       bin_start, lm);
-  // the tail is usually empty: a grid-stride loop
-  unsigned g = (unsigned)std::min<int64_t>((src.n + 255) / 256, 512);
-  hipLaunchKernelGGL(k_copy_tail<TS>, dim3(g), dim3(256), 0, st, src, dst, perm, bin_start, nbins);
-}
-
-template <typename TS>
-void launch_copy_tail(const PView<TS>& src, const PView<TS>& dst, const int64_t* bin_start, int64_t nbins,
-                      hipStream_t st, const uint32_t* perm) {
-  if (src.n == 0) return;
-  unsigned g = (unsigned)std::min<int64_t>((src.n + 255) / 256, 512);
-  hipLaunchKernelGGL(k_copy_tail<TS>, dim3(g), dim3(256), 0, st, src, dst, perm, bin_start, nbins);
-}
-
-template <typename TS>
-void launch_copy_particles(const PView<TS>& src, const PView<TS>& dst, hipStream_t st) {
-  if (src.n == 0) return;
-  unsigned g = (unsigned)std::min<int64_t>((src.n + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_copy_particles<TS>, dim3(g), dim3(256), 0, st, src, dst);
+void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, const int64_t* bin_start,
+                       uint32_t* lm, hipStream_t st) {
+  if (n == 0 || plan.ntiles == 0) return;
+  hipLaunchKernelGGL(k_level_perm, dim3(plan.ntiles), dim3(256), 0, st, plan.tiles_d, plan.tile, perm, bin_start, lm);
 }
 
 #define DUST_FUSED_INST(TS, A)                                                                    \
-  template void launch_fused<TS, A>(const FusedPlan&, const PView<TS>&, const PView<TS>&, bool,     \
+  template void launch_fused<TS, A>(const FusedPlan&, const PView<TS>&, const FusedMove<TS>&,       \
                                     const Box*, int, int, int, int, const FView<TS>&,              \
                                     const Forces&, const Species*, int, double, const double*,     \
-                                    const int64_t*, const double*, DiagDev*, bool, const uint32_t*, \
-                                    hipEvent_t, hipEvent_t, hipStream_t);                          \
+                                    const int64_t*, const double*, DiagDev*, bool, hipEvent_t,     \
+                                    hipEvent_t, hipStream_t);                                      \
   template void launch_halfstep_keys<TS, A>(const PView<TS>&, const Box*, int, int, int, int,       \
                                             const Forces&, double, const double*, int64_t,         \
-                                            TileShape, uint32_t*, hipStream_t);
+                                            TileShape, uint32_t*, const ShadowView<TS>&, hipStream_t);
 
 DUST_FUSED_INST(float, double)
 DUST_FUSED_INST(float, float)
 DUST_FUSED_INST(double, double)
 
-template void launch_level_perm<float>(const FusedPlan&, const PView<float>&, const PView<float>&,
-                                       const uint32_t*, const int64_t*, int64_t, uint32_t*,
-                                       hipStream_t);
-template void launch_level_perm<double>(const FusedPlan&, const PView<double>&, const PView<double>&,
-                                        const uint32_t*, const int64_t*, int64_t, uint32_t*,
-                                        hipStream_t);
-template void launch_copy_tail<float>(const PView<float>&, const PView<float>&, const int64_t*, int64_t,
-                                      hipStream_t, const uint32_t*);
-template void launch_copy_tail<double>(const PView<double>&, const PView<double>&, const int64_t*,
-                                       int64_t, hipStream_t, const uint32_t*);
-template void launch_copy_particles<float>(const PView<float>&, const PView<float>&, hipStream_t);
-template void launch_copy_particles<double>(const PView<double>&, const PView<double>&, hipStream_t);
+template void launch_reduce_fused<float>(const FusedPlan&, DiagDev*, bool, const PView<float>&,
+                                         const FusedMove<float>&, const int64_t*, hipStream_t);
+template void launch_reduce_fused<double>(const FusedPlan&, DiagDev*, bool, const PView<double>&,
+                                          const FusedMove<double>&, const int64_t*, hipStream_t);
 
 }  // namespace dust

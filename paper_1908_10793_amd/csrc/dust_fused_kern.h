@@ -136,6 +136,71 @@ __device__ __forceinline__ void load_raw(const PView<TS>& p, int64_t i, Raw<TS>&
   r.drag = p.drag ? p.drag[i] : TS(1);
 }
 
+// The same from the packed copy of a rebinning (one or two places of memory
+// instead of one per array).
+template <typename TS, int NDIM, int NC>
+__device__ __forceinline__ void load_raw(const ShadowView<TS>& sh, int64_t i, Raw<TS>& r) {
+  const ShadowRec<TS> s = sh.rec[i];
+  r.cell = s.cell;
+  r.species = s.species;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    r.off[d] = d < NDIM ? s.off[d] : TS(0);
+    r.mom[d] = d < NC ? s.mom[d] : TS(0);
+  }
+  r.id = 0;
+  r.mass = TS(0);
+  r.drag = TS(1);
+  if (sh.ext) {
+    const ShadowExt<TS> e = sh.ext[i];
+    r.id = e.id;
+    r.mass = e.mass;
+    r.drag = e.drag;
+  }
+}
+
+// Packs particle i (its cell, offsets and momenta as read) for a rebinning.
+template <typename TS, typename A>
+__device__ __forceinline__ void pack_particle(const PView<TS>& p, int64_t i, int64_t cell, const A off[3],
+                                              const A mom[3], const ShadowView<TS>& sh) {
+  ShadowRec<TS> r;
+  r.cell = (int32_t)cell;
+  r.species = p.species ? (int32_t)p.species[i] : 0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    r.off[d] = TS(off[d]);   // (read as TS: exact)
+    r.mom[d] = TS(mom[d]);
+  }
+  sh.rec[i] = r;
+  if (sh.ext) {
+    ShadowExt<TS> e{};
+    e.id = p.id ? p.id[i] : 0;
+    e.mass = p.mass ? p.mass[i] : TS(0);
+    e.drag = p.drag ? p.drag[i] : TS(1);
+    sh.ext[i] = e;
+  }
+}
+
+// The packed particle `from` into slot `to` of the arrays, unchanged.
+template <typename TS>
+__device__ __forceinline__ void unpack_particle(const ShadowView<TS>& sh, int64_t from, const PView<TS>& p,
+                                                int64_t to) {
+  const ShadowRec<TS> r = sh.rec[from];
+  p.cell[to] = r.cell;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    if (p.off[d]) p.off[d][to] = r.off[d];
+    if (p.mom[d]) p.mom[d][to] = r.mom[d];
+  }
+  if (p.species) p.species[to] = (uint8_t)r.species;
+  if (sh.ext) {
+    const ShadowExt<TS> e = sh.ext[from];
+    if (p.id) p.id[to] = e.id;
+    if (p.drag) p.drag[to] = e.drag;
+    if (p.mass) p.mass[to] = e.mass;
+  }
+}
+
 // Register budget: the FP32 kernel needs about 250 VGPRs (108 of them the
 // register sums); the compiler keeps the standard-form shapes but one under
 // 256 (2 waves/SIMD) by itself, and 4x4x16, the orbital-advection and the
@@ -150,7 +215,7 @@ constexpr int fused_waves_target() {
 template <typename TS, typename A, int GEOM, int NDIM, bool U, int TX, int TY, int TZ, bool FG>
 __global__ void __launch_bounds__(FUSED_THREADS)
     __attribute__((amdgpu_waves_per_eu(fused_waves_target<A, TS, GEOM, TX, TY, FG>())))
-    k_fused(const TileDesc* __restrict__ tiles, PView<TS> p, PView<TS> dst, int copy_attrs,
+    k_fused(const TileDesc* __restrict__ tiles, PView<TS> p, ShadowView<TS> sh, int clear_removed,
             const Box* __restrict__ boxes, FView<TS> fl, Forces f, const Species* __restrict__ sp,
             int drag_mode, A dt, const double* __restrict__ tdev,
             const int64_t* __restrict__ bin_start, const double* __restrict__ xg, DiagDev* dg,
@@ -160,10 +225,12 @@ __global__ void __launch_bounds__(FUSED_THREADS)
   // and never aliased by the particle and field arrays: __restrict__ lets
   // their fields stay in scalar registers / the scalar cache, so the loop's
   // waits on particle loads do not also wait on descriptor reloads.
-  // p: particles read; dst: where the updated particles are written, in the
-  // binned (level-major) slot order.  Slot i reads particle src_index[i] of
-  // p (right after a rebinning, dst != p), or particle i (src_index null, in
-  // place).  copy_attrs copies the attributes the step does not change.
+  // p: the particles, written in the binned (level-major) slot order.  Right
+  // after a rebinning (sh.rec given) slot i reads packed particle
+  // src_index[i] of sh, and the attributes the step does not change are
+  // written too; else particle i of p, in place.
+  const bool copy_attrs = sh.rec != nullptr;
+  const PView<TS>& dst = p;
   // FG: the forces are the orbital-advection shearing box (kernels of their
   // own, so that neither form's code costs the other registers)
   constexpr int nc = GEOM == GEOM_CART ? NDIM : 3;
@@ -268,23 +335,26 @@ __global__ void __launch_bounds__(FUSED_THREADS)
   Raw<TS> nxt;
   uint32_t nxt_si = 0, si_b = slot_b;
   if (wl.cnt > 0) {
-    nxt_si = src_index ? src_index[slot] : slot;
-    load_raw<TS, NDIM, nc>(p, nxt_si, nxt, copy_attrs);
+    nxt_si = copy_attrs ? src_index[slot] : slot;
+    if (copy_attrs) load_raw<TS, NDIM, nc>(sh, nxt_si, nxt);
+    else load_raw<TS, NDIM, nc>(p, nxt_si, nxt, false);
   }
-  if (src_index && wl.cnt > 1) si_b = src_index[slot_b];
+  if (copy_attrs && wl.cnt > 1) si_b = src_index[slot_b];
   // this thread's flags, raised once after the loop (no atomics in it)
   uint32_t flags_acc = 0;
   for (int j = 0; j < wl.nlev; ++j) {
     const bool has = wl.cnt > j;
-    const uint32_t i = slot;       // slot written
-    const uint32_t si = nxt_si;    // particle read
+    const uint32_t i = slot;
     const Raw<TS> cur = nxt;
     slot = slot_b;
     nxt_si = si_b;
     slot_b = level_slot(wl, j + 2, lvl);
-    if (wl.cnt > j + 1) load_raw<TS, NDIM, nc>(p, nxt_si, nxt, copy_attrs);   // next particle
+    if (wl.cnt > j + 1) {   // next particle
+      if (copy_attrs) load_raw<TS, NDIM, nc>(sh, nxt_si, nxt);
+      else load_raw<TS, NDIM, nc>(p, nxt_si, nxt, false);
+    }
     si_b = slot_b;
-    if (src_index && wl.cnt > j + 2) si_b = src_index[slot_b];               // and the index after
+    if (copy_attrs && wl.cnt > j + 2) si_b = src_index[slot_b];   // and the index after
     // Lanes of one wave walk different cells, so nothing below branches
     // around the register sums: a particle without a cell, or one that left
     // through an open face, continues as a dummy at the centre of this
@@ -332,8 +402,7 @@ __global__ void __launch_bounds__(FUSED_THREADS)
         if (lane == leader) base = atomicAdd(defer_count, (uint32_t)__popcll(dm));
         base = __shfl(base, leader, 64);
         if (deferred) {
-          defer_list[2 * (base + lanes_below(dm))] = i;
-          defer_list[2 * (base + lanes_below(dm)) + 1] = si;
+          defer_list[base + lanes_below(dm)] = i;
         }
       }
     }
@@ -531,6 +600,13 @@ __global__ void __launch_bounds__(FUSED_THREADS)
     if (live) {
       bool alive = drift<A, GEOM, NDIM, U, FG>(B, f, false, h, t0 + double(dt), idx, off, mom);
       store_particle<TS, A, GEOM, NDIM, FG>(dst, B, f, t0 + double(dt), i, alive, idx, off, mom, dg);
+      if (!alive && clear_removed) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          if (d < NDIM) dst.off[d][i] = TS(0);
+          if (d < nc) dst.mom[d][i] = TS(0);
+        }
+      }
     }
     if (copy_attrs && has && !deferred) {
       if (!live) {
@@ -629,7 +705,8 @@ __global__ void __launch_bounds__(FUSED_THREADS)
 // and the sticky flags go to dg directly, as in the tile kernel.
 template <typename TS, typename A, int GEOM, int NDIM, bool U>
 __global__ void __launch_bounds__(256)
-    k_fused_deferred(PView<TS> p, PView<TS> dst, int copy_attrs, const Box* __restrict__ boxes,
+    k_fused_deferred(PView<TS> p, ShadowView<TS> sh, const uint32_t* __restrict__ src_index,
+                     const Box* __restrict__ boxes,
                      int nbox, FView<TS> fl, Forces f, const Species* __restrict__ sp, int drag_mode,
                      A dt, const double* __restrict__ tdev, const double* __restrict__ xg,
                      const uint32_t* __restrict__ list, const uint32_t* __restrict__ count,
@@ -641,8 +718,12 @@ __global__ void __launch_bounds__(256)
   const A h = A(0.5) * dt;
   double s_j[3] = {0, 0, 0}, s_e = 0, s_abs = 0, s_cells = 0, s_n = 0;
   for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-    const int64_t i = list[2 * e], si = list[2 * e + 1];   // slot written, particle read
-    const int32_t cid = p.cell[si];
+    // slot; after a rebinning its packed particle is written there first,
+    // which then holds what the step does not change
+    const int64_t i = list[e];
+    if (sh.rec) unpack_particle(sh, src_index[i], p, i);
+    const PView<TS>& dst = p;
+    const int32_t cid = p.cell[i];
     const int b = find_box(boxes, nbox, cid);
     const Box& B = boxes[b];
     int idx[3];
@@ -651,8 +732,8 @@ __global__ void __launch_bounds__(256)
     bool bad = false;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      off[d] = d < NDIM ? A(p.off[d][si]) : A(0);
-      mom[d] = d < nc ? A(p.mom[d][si]) : A(0);
+      off[d] = d < NDIM ? A(p.off[d][i]) : A(0);
+      mom[d] = d < nc ? A(p.mom[d][i]) : A(0);
       bad |= !(off[d] >= A(-0.5) && off[d] < A(0.5));
     }
     if (bad) flag(dg, DUST_FLAG_OFFSET_RANGE);
@@ -711,11 +792,11 @@ __global__ void __launch_bounds__(256)
       A sl[3];
 #pragma unroll
       for (int m = 0; m < 3; ++m) sl[m] = m < nc ? slip_canonical<A, GEOM>(ss, m, v[m]) : A(0);
-      int spc = p.species ? p.species[si] : 0;
+      int spc = p.species ? p.species[i] : 0;
       if (spc >= sp->n) spc = 0;
-      const A m = p.mass ? A(p.mass[si]) : A(sp->mass[spc]);
+      const A m = p.mass ? A(p.mass[i]) : A(sp->mass[spc]);
       A it = drag_mode == DRAG_SPECIES ? A(sp->inv_tau[spc])
-                                       : inverse_tau<A, GEOM>(f, drag_mode, A(p.drag[si]), A(0), wh);
+                                       : inverse_tau<A, GEOM>(f, drag_mode, A(p.drag[i]), A(0), wh);
       A c, psi;
       propagator<A>(dt * it, c, psi);
       KickOut<A> o;
@@ -753,19 +834,6 @@ __global__ void __launch_bounds__(256)
     } else {
       store_particle_any<TS, A, GEOM, NDIM>(dst, B, f, t0 + double(h), i, false, idx, off, mom, dg);
     }
-    if (copy_attrs) {
-      if (!alive) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          if (d < NDIM) dst.off[d][i] = p.off[d][si];
-          if (d < nc) dst.mom[d][i] = p.mom[d][si];
-        }
-      }
-      if (p.drag) dst.drag[i] = p.drag[si];
-      if (p.mass) dst.mass[i] = p.mass[si];
-      if (p.species) dst.species[i] = p.species[si];
-      if (p.id) dst.id[i] = p.id[si];
-    }
   }
   // block partials (fixed order) into slot part0 + blockIdx.x
   __shared__ double red[4][PART_WORDS];
@@ -784,12 +852,11 @@ __global__ void __launch_bounds__(256)
 }
 
 template <typename TS, typename A, int GEOM, int NDIM, bool U, int TX, int TY, int TZ, bool FG>
-void launch_fused_t(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& q,
-                           bool copy_attrs, const Box* boxes_d,
+void launch_fused_t(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d,
                            const FView<TS>& fl, const Forces& f, const Species* sp, int drag_mode,
                            double dt, const double* tdev, const int64_t* bin_start, const double* xg,
                            DiagDev* dg, double* part, bool sums, uint32_t* defer_list,
-                           uint32_t* defer_count, const uint32_t* src_index, hipStream_t st) {
+                           uint32_t* defer_count, hipStream_t st) {
   constexpr int nc = GEOM == GEOM_CART ? NDIM : 3;
   size_t lds = fused_lds_bytes(plan, nc, (int)sizeof(TS));
   auto kern = k_fused<TS, A, GEOM, NDIM, U, TX, TY, TZ, FG>;
@@ -801,26 +868,25 @@ void launch_fused_t(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& 
       raised = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(FUSED_THREADS), lds, st, plan.tiles_d, p, q,
-                     (int)copy_attrs, boxes_d, fl, f, sp, drag_mode, A(dt), tdev, bin_start, xg, dg, part,
-                     (int)sums, defer_list, defer_count, src_index);
+  hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(FUSED_THREADS), lds, st, plan.tiles_d, p, mv.sh,
+                     mv.clear_removed, boxes_d, fl, f, sp, drag_mode, A(dt), tdev, bin_start, xg, dg, part,
+                     (int)sums, defer_list, defer_count, mv.src_index);
 }
 
 // One fused launch of every tile for one geometry (the tile kernel, then the
 // deferred-particle kernel); ev0 / ev1 bracket the tile kernel.
 template <typename TS, typename A, int GEOM, int NDIM, bool U>
-void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& q,
-                           bool copy_attrs, const Box* boxes_d,
+void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d,
                            const FView<TS>& fl, const Forces& f, const Species* sp, int drag_mode,
                            double dt, const double* tdev, const int64_t* bin_start, const double* xg,
                            DiagDev* dg, double* part, bool sums, uint32_t* defer_list,
-                           uint32_t* defer_count, const uint32_t* src_index, int nbox,
+                           uint32_t* defer_count, int nbox,
                            hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   if (ev0) (void)hipEventRecord(ev0, st);   // the tile kernel alone is timed
 #define DUST_FK(TX, TY, TZ, FK)                                                                    \
-  launch_fused_t<TS, A, GEOM, NDIM, U, TX, TY, TZ, FK>(plan, p, q, copy_attrs, boxes_d, fl, f, sp,    \
+  launch_fused_t<TS, A, GEOM, NDIM, U, TX, TY, TZ, FK>(plan, p, mv, boxes_d, fl, f, sp,               \
                                                        drag_mode, dt, tdev, bin_start, xg, dg, part, \
-                                                       sums, defer_list, defer_count, src_index, st)
+                                                       sums, defer_list, defer_count, st)
 #define DUST_F(TX, TY, TZ) DUST_FK(TX, TY, TZ, false)
   if constexpr (NDIM == 3 && GEOM == GEOM_CART) {
     // the orbital-advection shearing box has kernels of its own
@@ -859,8 +925,8 @@ void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& 
 #undef DUST_F
 #undef DUST_FK
   if (ev1) (void)hipEventRecord(ev1, st);
-  hipLaunchKernelGGL((k_fused_deferred<TS, A, GEOM, NDIM, U>), dim3(DEFER_BLOCKS), dim3(256), 0, st, p, q,
-                     (int)copy_attrs, boxes_d, nbox, fl, f, sp, drag_mode, A(dt), tdev, xg,
+  hipLaunchKernelGGL((k_fused_deferred<TS, A, GEOM, NDIM, U>), dim3(DEFER_BLOCKS), dim3(256), 0, st, p, mv.sh,
+                     mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, A(dt), tdev, xg,
                      (const uint32_t*)defer_list, (const uint32_t*)defer_count, part, plan.ntiles, (int)sums,
                      dg);
 }
@@ -870,9 +936,9 @@ void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const PView<TS>& 
 // group, declared extern where it is called).
 #define DUST_FUSED_G_DECL(PREFIX, TS, A, G, D, UU)                                                      \
   PREFIX template void launch_fused_g<TS, A, G, D, UU>(                                               \
-      const FusedPlan&, const PView<TS>&, const PView<TS>&, bool, const Box*, const FView<TS>&,       \
+      const FusedPlan&, const PView<TS>&, const FusedMove<TS>&, const Box*, const FView<TS>&,         \
       const Forces&, const Species*, int, double, const double*, const int64_t*, const double*,       \
-      DiagDev*, double*, bool, uint32_t*, uint32_t*, const uint32_t*, int, hipEvent_t, hipEvent_t,     \
+      DiagDev*, double*, bool, uint32_t*, uint32_t*, int, hipEvent_t, hipEvent_t,                      \
       hipStream_t);
 #define DUST_FUSED_G_ALL(PREFIX, TS, A)                                                                \
   DUST_FUSED_G_DECL(PREFIX, TS, A, GEOM_CART, 2, true)                                                 \
