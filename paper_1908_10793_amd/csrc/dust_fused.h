@@ -65,7 +65,8 @@ static constexpr size_t FUSED_STATIC_LDS = 5 * 256 * sizeof(double) + 3 * DUST_M
 
 // One fused step over every tile (binned by tile-major key, bin_start).
 // After a rebinning (sh.rec given): slot s of p receives the update of the
-// packed particle src_index[s], attributes too, and the slots from
+// packed particle src_index[s] (or slot slot_of[t] that of perm[t]: a particle
+// per lane, dust_cells_kern.h), attributes too, and the slots from
 // bin_start[nbins] on (no tile visits them) the packed particles perm[s];
 // else the particles of p are updated in place.  clear_removed: a particle
 // that leaves in the second half drift of a rebinning step keeps whatever its
@@ -74,8 +75,9 @@ static constexpr size_t FUSED_STATIC_LDS = 5 * 256 * sizeof(double) + 3 * DUST_M
 // around the tile kernel alone (not the deferred-particle kernel).
 template <typename TS> struct FusedMove {
   ShadowView<TS> sh;
-  const uint32_t* src_index;
+  const uint32_t* src_index;   // null: slot_of is given instead
   const uint32_t* perm;
+  const uint32_t* slot_of;     // slot of each sorted position
   int64_t nbins;
   int clear_removed;
 };
@@ -96,9 +98,13 @@ void launch_halfstep_keys(const PView<TS>& p, const Box* boxes_d, int nbox, int 
 
 // After the sort (perm, bin_start): lm = the source index of every binned
 // slot in the fused kernel's level-major layout within each wave's range of
-// slots.
+// slots; inverse: instead the slot of every sorted position.
 void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, const int64_t* bin_start,
-                       uint32_t* lm, hipStream_t st);
+                       uint32_t* lm, bool inverse, hipStream_t st);
+
+// Whether a rebinning step of n particles over `cells` active cells runs a
+// particle per lane (dust_cells_kern.h) or a cell per thread.
+bool cells_path(int64_t n, int64_t cells);
 
 // Adds the per-workgroup diagnostic partials of the last fused launch (tile
 // kernel and deferred kernel) to the diagnostics block, and resets the

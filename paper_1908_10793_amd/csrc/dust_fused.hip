@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "dust_cells_kern.h"
 #include "dust_fused_kern.h"
 
 namespace dust {
@@ -184,6 +185,12 @@ __global__ void __launch_bounds__(REDUCE_THREADS)
 DUST_FUSED_G_ALL(extern, float, double)
 DUST_FUSED_G_ALL(extern, float, float)
 DUST_FUSED_G_ALL(extern, double, double)
+DUST_CELLS_ALL(extern, float, double)
+DUST_CELLS_ALL(extern, float, float)
+DUST_CELLS_ALL(extern, double, double)
+
+// Largest mean of particles per cell for the particle-per-lane kernel.
+static constexpr int64_t CELLS_PPC = 24;
 
 template <typename TS, typename A>
 void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
@@ -194,6 +201,28 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
   double* part = plan.part_d;
   // (the deferred-particle count is zero here: set at set-up, and reset by
   // the partial reduction that ends every launch)
+  if (mv.sh.rec && mv.slot_of) {
+    if (ev0) (void)hipEventRecord(ev0, st);
+#define DUST_G(G, D, UU)                                                                                   \
+  do {                                                                                                     \
+    launch_cells_g<TS, A, G, D, UU>(plan, p, mv, boxes_d, fl, f, sp, drag_mode, dt, tdev, bin_start, xg, dg, \
+                                    sums, st);                                                             \
+    if (ev1) (void)hipEventRecord(ev1, st);                                                                \
+    hipLaunchKernelGGL((k_fused_deferred<TS, A, G, D, UU>), dim3(DEFER_BLOCKS), dim3(256), 0, st, p,       \
+                       ShadowView<TS>{nullptr, nullptr}, (const uint32_t*)nullptr, boxes_d, nbox, fl, f, sp, \
+                       drag_mode, A(dt), tdev, xg, (const uint32_t*)plan.defer_list,                       \
+                       (const uint32_t*)plan.defer_count, part, plan.ntiles, (int)sums, dg);               \
+  } while (0)
+    if (geom == GEOM_CART && ndim == 2 && unif) DUST_G(GEOM_CART, 2, true);
+    else if (geom == GEOM_CART && ndim == 2) DUST_G(GEOM_CART, 2, false);
+    else if (geom == GEOM_CART && unif) DUST_G(GEOM_CART, 3, true);
+    else if (geom == GEOM_CART) DUST_G(GEOM_CART, 3, false);
+    else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
+    else DUST_G(GEOM_SPH, 3, false);
+#undef DUST_G
+    launch_reduce_fused<TS>(plan, dg, sums, p, mv, bin_start, st);
+    return;
+  }
 #define DUST_G(G, D, UU)                                                                          \
   launch_fused_g<TS, A, G, D, UU>(plan, p, mv, boxes_d, fl, f, sp, drag_mode, dt, tdev,            \
                                   bin_start, xg, dg, part, sums, plan.defer_list,                  \
@@ -289,10 +318,10 @@ void launch_halfstep_keys(const PView<TS>& p, const Box* boxes_d, int nbox, int 
 // The level-major order of each tile's binned particles as a permutation:
 // lm[slot] = perm[ps + j] for the j-th particle of a cell whose sorted range
 // starts at ps (one workgroup per tile, one thread per cell: the fused
-// kernel's mapping).
+// kernel's mapping); inverse: lm[ps + j] = slot.
 __global__ void __launch_bounds__(256)
     k_level_perm(const TileDesc* __restrict__ tiles, TileShape ts, const uint32_t* __restrict__ perm,
-                 const int64_t* __restrict__ bin_start, uint32_t* __restrict__ lm) {
+                 const int64_t* __restrict__ bin_start, uint32_t* __restrict__ lm, int inverse) {
   const TileDesc td = tiles[blockIdx.x];
   const int TX = ts.t[0], TY = ts.t[1];
   const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
@@ -307,15 +336,21 @@ __global__ void __launch_bounds__(256)
   uint32_t lvl = wl.base;
   for (int j = 0; j < wl.nlev; ++j) {
     const uint32_t to = level_slot(wl, j, lvl);
-    if (wl.cnt > j) lm[to] = perm[ps + j];
+    if (wl.cnt > j) {
+      if (inverse) lm[ps + j] = to;
+      else lm[to] = perm[ps + j];
+    }
   }
 }
 
 void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, const int64_t* bin_start,
-                       uint32_t* lm, hipStream_t st) {
+                       uint32_t* lm, bool inverse, hipStream_t st) {
   if (n == 0 || plan.ntiles == 0) return;
-  hipLaunchKernelGGL(k_level_perm, dim3(plan.ntiles), dim3(256), 0, st, plan.tiles_d, plan.tile, perm, bin_start, lm);
+  hipLaunchKernelGGL(k_level_perm, dim3(plan.ntiles), dim3(256), 0, st, plan.tiles_d, plan.tile, perm, bin_start, lm,
+                     (int)inverse);
 }
+
+bool cells_path(int64_t n, int64_t cells) { return n <= CELLS_PPC * cells; }
 
 #define DUST_FUSED_INST(TS, A)                                                                    \
   template void launch_fused<TS, A>(const FusedPlan&, const PView<TS>&, const FusedMove<TS>&,       \

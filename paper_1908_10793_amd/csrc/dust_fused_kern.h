@@ -940,6 +940,10 @@ void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const FusedMove<T
       const Forces&, const Species*, int, double, const double*, const int64_t*, const double*,       \
       DiagDev*, double*, bool, uint32_t*, uint32_t*, int, hipEvent_t, hipEvent_t,                      \
       hipStream_t);
+#define DUST_DEFERRED_DECL(PREFIX, TS, A, G, D, UU)                                                     \
+  PREFIX template __global__ void k_fused_deferred<TS, A, G, D, UU>(                                  \
+      PView<TS>, ShadowView<TS>, const uint32_t*, const Box*, int, FView<TS>, Forces, const Species*, \
+      int, A, const double*, const double*, const uint32_t*, const uint32_t*, double*, int, int, DiagDev*);
 #define DUST_FUSED_G_ALL(PREFIX, TS, A)                                                                \
   DUST_FUSED_G_DECL(PREFIX, TS, A, GEOM_CART, 2, true)                                                 \
   DUST_FUSED_G_DECL(PREFIX, TS, A, GEOM_CART, 2, false)                                                \

@@ -12,13 +12,9 @@
 //    order, whatever their cells hold (no imbalance where dust collects),
 //    and walks them in chunks of 256, tile by tile, with an FP64 LDS window
 //    over the tile and one cell around it;
-//  * one lane per particle forms its weights and its channels' values and
-//    puts them in LDS (the next chunk's particles are loaded meanwhile);
-//    then nine lanes take a particle, one lane per row of three cells of its
-//    stencil (2-D: per cell), seven particles of a wave at a time, and sum in
-//    registers until the host cell changes.  A lane holds one row's channels
-//    (12 registers where a thread per host cell needs 108), so FP64 sums
-//    cost no occupancy, and lanes never wait for the fullest cell of a wave;
+//  * one lane per particle forms its weights and its channels' values (the
+//    next chunk's particles are loaded meanwhile), and the chunk is summed by
+//    runs of one host cell (dust_runsum.h);
 //  * a run of one host cell is then added to the window, and the window to
 //    HBM once per tile.
 #pragma once
@@ -28,11 +24,12 @@
 #include "dust_device.h"
 #include "dust_launch.h"
 #include "dust_particle.h"
+#include "dust_runsum.h"
 #include "dust_sorted.h"
 
 namespace dust {
 
-static constexpr int SORTED_THREADS = 256;   // also the particles of a chunk
+static constexpr int SORTED_THREADS = RUN_THREADS;   // also the particles of a chunk
 
 // Three velocity components and the density of a window's cell, in the
 // storage type; the unfused step in Cartesian boxes takes the arithmetic type
@@ -50,30 +47,7 @@ template <typename TS, typename A, int GEOM, int NDIM, int MODE> struct SortedSh
   static constexpr int RX = T0 + 2, RY = T1 + 2, RZ = NDIM > 2 ? T2 + 2 : 1;
   static constexpr int WC = RX * RY * RZ;
   static constexpr int NT = NDIM > 2 ? 27 : 9;    // cells of a stencil
-  // a stencil over 9 lanes: a row of NA = 3 cells each (2-D: one cell)
-  static constexpr int NA = NDIM > 2 ? 3 : 1;
-  static constexpr int GROUPS = 7;                // particles that a wave takes at a time
-  // a wave's 64 particles go through its records in one round, FP64 in two
-  // (with the records of 64, one workgroup less would fit a CU's LDS)
-  static constexpr int ROUNDS = sizeof(A) == 4 ? 1 : 2;
-  static constexpr int RP = 64 / ROUNDS;          // particles of a round
-  static constexpr int PG = (RP + GROUPS - 1) / GROUPS;   // a group's share of them
-  // one particle's words: q[4], w0[3] and a pad, then FP32 the 9 products w1
-  // w2 at a stride of 20 words, FP64 w1[3], w2[3] at 14 (no pad): consecutive
-  // lanes' 16-byte writes, and the seven groups' reads, on distinct banks
-  static constexpr bool F32 = sizeof(A) == 4;
-  static constexpr int RS = F32 ? 20 : 14;
-  static constexpr int W0 = 4, W1 = F32 ? 8 : 7, W2 = 10;
-  static constexpr int WR = GROUPS * PG;          // records of a wave (those past RP stay zero)
 };
-
-// A wave's LDS writes before this, its reads after (its LDS operations
-// complete in order; this keeps the compiler's order).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Stored state of one particle, as loaded a chunk ahead.
 template <typename TS, typename TW> struct SortedRaw {
@@ -127,26 +101,17 @@ __global__ void __launch_bounds__(SORTED_THREADS) __attribute__((amdgpu_waves_pe
              DiagDev* dg, int sums) {
   using S = SortedShape<TS, A, GEOM, NDIM, MODE>;
   using TG = typename S::TG;
-  constexpr int NC = S::NC, NCH = S::NCH, NA = S::NA, PG = S::PG, RX = S::RX, RY = S::RY, WC = S::WC;
+  constexpr int NC = S::NC, NCH = S::NCH, RX = S::RX, RY = S::RY, WC = S::WC;
   constexpr int c2 = NDIM > 2 ? 1 : 0;
-  constexpr bool F32 = S::F32;
   __shared__ double win[NCH * WC];
-  __shared__ __align__(16) A rec[(SORTED_THREADS / 64) * S::WR * S::RS];
-  __shared__ int s_r[SORTED_THREADS];
+  __shared__ __align__(16) A rec[RunSums<A, NDIM>::WORDS];
   __shared__ GasCell<TG> gas[S::GAS ? WC : 1];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int64_t s0 = (int64_t)blockIdx.x * ppb;
   const int64_t s1 = s0 + ppb < p.n ? s0 + ppb : p.n;
   uint32_t flags = 0;
   double sum[5] = {0, 0, 0, 0, 0}, cells = 0.0;   // SORTED_STEP: the kick's diagnostics
-  // this lane's row of the stencil (2-D: cell), relative to the host cell
-  const int grp = lane / 9, row = lane % 9;
-  const bool sums_lane = grp < S::GROUPS;
-  const int rb = NDIM > 2 ? row % 3 : row / 3, rc = NDIM > 2 ? row / 3 : 0;   // y and z of the row
-  const int ra = NDIM > 2 ? 0 : row % 3;                                      // x of its first cell
-  const int soff = (ra - 1) + RX * ((rb - 1) + RY * (rc - c2));
-  // the records past a round's particles stay zero
-  for (int r = lane; r < (S::WR - S::RP) * S::RS; r += 64) rec[(wave * S::WR + S::RP) * S::RS + r] = A(0);
+  run_sums_init<A, NDIM>(rec);
 
   // the tile in the window: its box, cells, first window cell, end of its keys
   int ub = 0, e0 = 0, e1 = 0, e2 = 0, o0 = 0, o1 = 0, o2 = 0;
@@ -339,82 +304,7 @@ __global__ void __launch_bounds__(SORTED_THREADS) __attribute__((amdgpu_waves_pe
           }
         }
       }
-      s_r[tid] = r0;
-      // where runs of one host cell start (the first particle of a group's
-      // share always does); a wave reads its own records only
-      const int prev = __shfl_up(r0, 1);
-      const uint64_t starts_all = __ballot(has && ((lane % S::RP) % PG == 0 || r0 != prev));
-#pragma unroll
-      for (int rd = 0; rd < S::ROUNDS; ++rd) {
-        const uint64_t starts = S::ROUNDS == 1 ? starts_all : (starts_all >> (rd * S::RP)) & 0xffffffffull;
-        if (starts == 0) continue;   // (wave-uniform: no particle in this round)
-        uint32_t any = 0;   // iterations at which a run starts in some group
-#pragma unroll
-        for (int g = 0; g < S::GROUPS; ++g) any |= (uint32_t)(starts >> (g * PG)) & ((1u << PG) - 1);
-        // the records (a thread without a particle here: zeros, which add nothing)
-        if (S::ROUNDS == 1 || lane / S::RP == rd) {
-          A* rw = rec + (wave * S::WR + lane % S::RP) * S::RS;
-#pragma unroll
-          for (int m = 0; m < 4; ++m) rw[m] = q[m];
-#pragma unroll
-          for (int a = 0; a < 3; ++a) rw[S::W0 + a] = st.w[0][a];
-          if constexpr (F32) {
-#pragma unroll
-            for (int a = 0; a < 9; ++a) rw[S::W1 + a] = st.w[1][a % 3] * st.w[2][NDIM > 2 ? a / 3 : 1];
-          } else {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-              rw[S::W1 + a] = st.w[1][a];
-              rw[S::W2 + a] = st.w[2][a];
-            }
-          }
-        }
-        wave_lds_fence();
-        const uint32_t mine = sums_lane ? (uint32_t)(starts >> (grp * PG)) & ((1u << PG) - 1) : 0u;
-        const A* rr = rec + (wave * S::WR + (sums_lane ? grp : 0) * PG) * S::RS;
-        const int* rh = s_r + wave * 64 + rd * S::RP + (sums_lane ? grp : 0) * PG;
-        A acc[NA][NCH];
-        int host = -1;
-        auto flush = [&]() {
-#pragma unroll
-          for (int a = 0; a < NA; ++a)
-#pragma unroll
-            for (int m = 0; m < NCH; ++m) atomicAdd(&win[m * WC + host + soff + a], double(acc[a][m]));
-        };
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-          for (int m = 0; m < NCH; ++m) acc[a][m] = A(0);
-#pragma unroll 5
-        for (int j = 0; j < PG; ++j) {
-          const A* w = rr + j * S::RS;
-          A qj[NCH], wx[NA], wyz;
-#pragma unroll
-          for (int m = 0; m < NCH; ++m) qj[m] = w[m];
-#pragma unroll
-          for (int a = 0; a < NA; ++a) wx[a] = w[S::W0 + ra + a];
-          if constexpr (F32) wyz = w[S::W1 + rb + 3 * rc];
-          else wyz = w[S::W1 + rb] * w[S::W2 + (NDIM > 2 ? rc : 1)];
-          if ((any >> j) & 1u) {   // (wave-uniform)
-            if ((mine >> j) & 1u) {
-              if (host >= 0) flush();
-              host = rh[j];
-#pragma unroll
-              for (int a = 0; a < NA; ++a)
-#pragma unroll
-                for (int m = 0; m < NCH; ++m) acc[a][m] = A(0);
-            }
-          }
-#pragma unroll
-          for (int m = 0; m < NCH; ++m) {
-            const A t = wyz * qj[m];
-#pragma unroll
-            for (int a = 0; a < NA; ++a) acc[a][m] += wx[a] * t;
-          }
-        }
-        if (host >= 0) flush();
-        if (S::ROUNDS > 1) wave_lds_fence();   // (the next round's records)
-      }
+      run_sums<A, NDIM, NCH>(win, RX, RY, WC, rec, r0, has, q, st);
       done += cnt;
     }
   }
