@@ -685,7 +685,9 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
   DiagDev* dg = (flags & DUST_STEP_DIAG) ? c->diag : nullptr;
   constexpr bool f32 = std::is_same<TS, float>::value && std::is_same<A, float>::value;
   const bool c3 = use_c3(c, f32, F, pv);
-  FusedMove<TS> mv{sh, nullptr, nullptr, nullptr, c->n_active, 0};
+  FusedMove<TS> mv{};
+  mv.sh = sh;
+  mv.nbins = c->n_active;
   // Rebinning: keys of the cells the particles kick in and their packed copy,
   // a stable sort, and the source index of every slot in the fused kernel's
   // order.
@@ -699,12 +701,19 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
                                   c->n_active, c->tile, c->bin.key[0], sh, st);
     c->bin_cur = launch_bin(pv.cell, pv.n, c->boxes_d, c->nbox, c->n_active, DUST_BIN_TILE, c->tile,
                             c->bin, nullptr, c->bin_start, true, st);
-    uint32_t* lm = c->bin.val[1 - c->bin_cur];   // free once the sort is done
-    const bool cells = !c3 && cells_path(pv.n, c->n_active);
-    if (c3) launch_c3_level_perm(c->plan, c->bin.val[c->bin_cur], c->bin_start, lm, st);
-    else launch_level_perm(c->plan, pv.n, c->bin.val[c->bin_cur], c->bin_start, lm, cells, st);
+    // (the other buffers are free once the sort is done)
+    uint32_t* lm = c->bin.val[1 - c->bin_cur];
+    uint32_t* lm2 = c->bin.key[1 - c->bin_cur];
+    const bool cells = cells_path(pv.n, c->n_active);
+    if (c3) {
+      launch_c3_level_perm(c->plan, c->bin.val[c->bin_cur], c->bin_start, lm, cells ? lm2 : nullptr, st);
+      mv.order_src = cells ? lm : nullptr;
+      mv.slot_of = cells ? lm2 : nullptr;
+    } else {
+      launch_level_perm(c->plan, pv.n, c->bin.val[c->bin_cur], c->bin_start, lm, cells, st);
+      mv.slot_of = cells ? lm : nullptr;
+    }
     mv.src_index = cells ? nullptr : lm;
-    mv.slot_of = cells ? lm : nullptr;
     mv.perm = c->bin.val[c->bin_cur];
     mv.clear_removed = c->shadow_new;
     c->shadow_new = false;

@@ -11,7 +11,9 @@ DUST_C3_AUX_SHAPES(extern)
 
 // Rebinning: order the cells of every tile for the tile kernel's threads
 // into tmap, and write lm[slot] = perm[ps + j], the source of every slot of
-// the level-major layout that c3_layout describes.
+// the level-major layout that c3_layout describes; with order_slot the same
+// pairs lane by lane instead (lm[k] the source, order_slot[k] the slot of the
+// tile's k-th particle when its cells are taken in lane order).
 //
 // A wave runs as many levels as its fullest cell, so its cells should have
 // similar counts; and its 64 lanes read the gas window at their cells'
@@ -24,7 +26,7 @@ DUST_C3_AUX_SHAPES(extern)
 __global__ void __launch_bounds__(256)
     k_c3_level_perm(const TileDesc* __restrict__ tiles, const uint32_t* __restrict__ perm,
                     const int64_t* __restrict__ bin_start, uint8_t* __restrict__ tmap,
-                    uint32_t* __restrict__ lm, int rx, int ry) {
+                    uint32_t* __restrict__ lm, uint32_t* __restrict__ order_slot, int rx, int ry) {
   __shared__ int cnt_s[256];
   __shared__ int grp_s[256];
   __shared__ int gsize[16];
@@ -64,6 +66,17 @@ __global__ void __launch_bounds__(256)
   int64_t ps;
   const WaveLevels wl = c3_layout(td, lc, bin_start, ps);
   uint32_t lvl = wl.base;
+  // this lane's first place lane by lane: the counts of the wave's lower lanes
+  uint32_t first = wl.base;
+  if (order_slot) {
+    int incl = wl.cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if ((t & 63) >= o) incl += u;
+    }
+    first += (uint32_t)(incl - wl.cnt);
+  }
   // four levels at a time: a lane's four sources share a cache line, and
   // their loads issue together
   for (int j0 = 0; j0 < wl.nlev; j0 += 4) {
@@ -74,7 +87,14 @@ __global__ void __launch_bounds__(256)
     for (int q = 0; q < 4; ++q) {
       if (j0 + q >= wl.nlev) break;   // (wave-uniform)
       const uint32_t to = level_slot(wl, j0 + q, lvl);
-      if (wl.cnt > j0 + q) lm[to] = src[q];
+      if (wl.cnt > j0 + q) {
+        if (order_slot) {
+          lm[first + j0 + q] = src[q];
+          order_slot[first + j0 + q] = to;
+        } else {
+          lm[to] = src[q];
+        }
+      }
     }
   }
 }
@@ -129,6 +149,10 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
   if (ev0) (void)hipEventRecord(ev0, st);
 #define DUST_C3(TX, TY, TZ)                                                                             \
   launch_c3_shape<TX, TY, TZ>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st)
+  const bool cells = mv.sh.rec && mv.order_src;
+  if (cells)
+    launch_c3_cells(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st);
+  else
   switch (plan.shape) {
     case 0: DUST_C3(8, 8, 4); break;
     case 1: DUST_C3(16, 4, 4); break;
@@ -140,7 +164,7 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
 #undef DUST_C3
   if (ev1) (void)hipEventRecord(ev1, st);
   hipLaunchKernelGGL((k_fused_deferred<float, float, GEOM_CART, 3, true>), dim3(DEFER_BLOCKS), dim3(256), 0, st,
-                     p, mv.sh, mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
+                     p, cells ? ShadowView<float>{nullptr, nullptr} : mv.sh, mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
                      (const uint32_t*)plan.defer_list, (const uint32_t*)plan.defer_count, plan.part_d,
                      plan.ntiles, (int)sums, dg);
   launch_reduce_fused<float>(plan, dg, sums, p, mv, bin_start, st);
@@ -171,10 +195,10 @@ void launch_c3_keys(const PView<float>& p, const Box* boxes_d, int nbox, double 
 }
 
 void launch_c3_level_perm(const FusedPlan& plan, const uint32_t* perm, const int64_t* bin_start,
-                          uint32_t* lm, hipStream_t st) {
+                          uint32_t* lm, uint32_t* order_slot, hipStream_t st) {
   if (plan.ntiles > 0)
     hipLaunchKernelGGL(k_c3_level_perm, dim3(plan.ntiles), dim3(256), 0, st, plan.tiles_d, perm, bin_start,
-                       plan.tile_map, lm, plan.tile.t[0] + 2 * FUSED_HALO, plan.tile.t[1] + 2 * FUSED_HALO);
+                       plan.tile_map, lm, order_slot, plan.tile.t[0] + 2 * FUSED_HALO, plan.tile.t[1] + 2 * FUSED_HALO);
 }
 
 }  // namespace dust

@@ -77,7 +77,8 @@ template <typename TS> struct FusedMove {
   ShadowView<TS> sh;
   const uint32_t* src_index;   // null: slot_of is given instead
   const uint32_t* perm;
-  const uint32_t* slot_of;     // slot of each sorted position
+  const uint32_t* slot_of;     // slot of each sorted position (FP32 uniform-Cartesian path: of each of
+  const uint32_t* order_src;   // order_src, the same particles lane by lane of the layout)
   int64_t nbins;
   int clear_removed;
 };
@@ -122,13 +123,18 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
                const Box* boxes_d, int nbox, const FView<float>& fl, const Forces& f, const Species* sp,
                int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
                DiagDev* dg, bool sums, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
+// The same after a rebinning with a particle per lane (dust_cart3_cells.hip).
+void launch_c3_cells(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv, const Box* boxes_d,
+                     const FView<float>& fl, const Forces& f, const Species* sp, double dt, const double* tdev,
+                     const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, hipStream_t st);
 // Its rebinning: half-step tile keys with its own drift (and the packed
 // particles), and after the sort the per-tile ranking of cells by count
-// (plan.tile_map) with the source index of every slot (lm).
+// (plan.tile_map) with the source index of every slot (lm), or with order_slot
+// given: lm the source indices lane by lane, order_slot their slots.
 void launch_c3_keys(const PView<float>& p, const Box* boxes_d, int nbox, double dt, int64_t nbins,
                     TileShape ts, uint32_t* key, const ShadowView<float>& sh, hipStream_t st);
 void launch_c3_level_perm(const FusedPlan& plan, const uint32_t* perm, const int64_t* bin_start, uint32_t* lm,
-                          hipStream_t st);
+                          uint32_t* order_slot, hipStream_t st);
 // Predictor drag source (mass: dust density) on the binned layout of the
 // last fused step (see k_c3_aux): out[0..2] the momentum deposit channels
 // (mass: out[0] the density array).
