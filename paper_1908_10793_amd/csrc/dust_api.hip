@@ -366,8 +366,7 @@ dust_status_t ensure_bin(Ctx* c, int64_t n) {
   if (c->bin_mem) HIP_TRY(hipFree(c->bin_mem));
   c->bin_mem = nullptr;
   int64_t nn = std::max<int64_t>(n, 1);
-  int64_t nblocks = bin_blocks(nn);
-  size_t hist = (size_t)256 * nblocks;
+  size_t hist = bin_hist_words(nn, false);
   size_t scan = bin_scan_tmp_words((int64_t)hist);
   auto rup = [](size_t b) { return (b + 255) & ~(size_t)255; };
   size_t bytes = 4 * rup((size_t)nn * 4) + rup(hist * 4) + rup(scan * 4) + rup((size_t)nn * 8);
@@ -381,6 +380,7 @@ dust_status_t ensure_bin(Ctx* c, int64_t n) {
   c->bin.hist = (uint32_t*)take(hist * 4);
   c->bin.scan_tmp = (uint32_t*)take(scan * 4);
   c->bin.gather_tmp = take((size_t)nn * 8);
+  c->bin.hist_words = hist;
   c->bin.cap_n = (size_t)nn;
   return DUST_OK;
 }
@@ -532,7 +532,7 @@ void* scratch_of(int device) {
 // false if it would not fit.
 bool scratch_work(void* base, int64_t n, BinWork& w) {
   const int64_t nn = std::max<int64_t>(n, 1);
-  const size_t hist = (size_t)256 * bin_blocks(nn);
+  const size_t hist = bin_hist_words(nn, true);
   const size_t scan = bin_scan_tmp_words((int64_t)hist);
   auto rup = [](size_t b) { return (b + 255) & ~(size_t)255; };
   const size_t bytes = 4 * rup((size_t)nn * 4) + rup(hist * 4) + rup(scan * 4) + rup((size_t)nn * 8);
@@ -546,6 +546,7 @@ bool scratch_work(void* base, int64_t n, BinWork& w) {
   w.hist = (uint32_t*)take(hist * 4);
   w.scan_tmp = (uint32_t*)take(scan * 4);
   w.gather_tmp = take((size_t)nn * 8);
+  w.hist_words = hist;
   w.cap_n = (size_t)nn;
   return true;
 }

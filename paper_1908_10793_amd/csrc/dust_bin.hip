@@ -1,9 +1,20 @@
-// Stable counting sort of particles by cell (or tile-major cell) key: an
-// LSD radix sort with 8-bit digits over as many passes as the key range
-// needs.  Each pass: per-block digit histograms, one exclusive scan over
-// (digit, block), and a scatter in which every block ranks its elements
-// stably (wave ballots for lanes, LDS counters across waves and chunks).
-// Deterministic: no atomics decide an order.
+// Stable counting sort of particles by cell (or tile-major cell) key: an LSD
+// radix sort with as few passes as digits of up to 9 bits need.  Each pass:
+// per-block digit histograms, one exclusive scan over (digit, block), and a
+// scatter in which every wave ranks its own keys stably (wave ballots, LDS
+// counters of its own), so that a block meets at five barriers and not at
+// three per 256 keys.  Deterministic: no atomics decide an order.
+//
+// Blocks are dealt to the XCDs in contiguous ranges (blockIdx mod 8 picks the
+// XCD): a digit's output of one block continues that of the block before, and
+// with both on one XCD its L2 joins their pieces into whole lines.  Measured
+// for 33.5 M keys of 24 bits, us per pass: 303 with 4096 keys a block in plain
+// order, ranked in step by the whole block (as this sort began); 315 with 8192
+// keys a block ranked wave by wave (2 waves per SIMD); 205 with 4096.  Digits
+// of 11 bits save a pass from 19 bits on, but cost 250 us a pass for 16.7 M
+// keys against 105 with 8 (the histograms and their scan grow by 8).
+#include <algorithm>
+
 #include "dust_device.h"
 #include "dust_launch.h"
 #include "dust_particle.h"
@@ -11,124 +22,202 @@
 namespace dust {
 
 static constexpr int BIN_THREADS = 256;
-static constexpr int BIN_ITEMS = 16;
-static constexpr int BIN_TILE = BIN_THREADS * BIN_ITEMS;  // elements per block
+static constexpr int BIN_WAVES = BIN_THREADS / 64;
+static constexpr int BIN_MAX_BITS = 9;
+// below this many keys, blocks of 1024 instead of 4096 (4096 would leave CUs idle)
+static constexpr int64_t BIN_FEW = 1 << 19;
 
-__global__ void k_make_keys(const int32_t* cell, int64_t n, const Box* boxes, int nbox,
-                            uint32_t nbins, int key_mode, TileShape ts, uint32_t* key) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int64_t c = cell[i];
-  uint32_t k = nbins;
-  if (c >= 0 && c < (int64_t)nbins) {
-    if (key_mode == DUST_BIN_TILE) {
-      int b = find_box(boxes, nbox, c);
-      k = tile_key(boxes[b], c - boxes[b].cell_base, ts);
-    } else {
-      k = (uint32_t)c;
+// Sort keys from the cells, KEYS_PER particles of a thread (their loads
+// issue together).
+static constexpr int KEYS_PER = 4;
+__global__ void __launch_bounds__(BIN_THREADS)
+    k_make_keys(const int32_t* __restrict__ cell, int64_t n, const Box* __restrict__ boxes, int nbox,
+                uint32_t nbins, int key_mode, TileShape ts, uint32_t* __restrict__ key) {
+  const int64_t i0 = (int64_t)blockIdx.x * (BIN_THREADS * KEYS_PER) + threadIdx.x;
+  int32_t c[KEYS_PER];
+#pragma unroll
+  for (int q = 0; q < KEYS_PER; ++q) {
+    const int64_t i = i0 + q * BIN_THREADS;
+    c[q] = i < n ? cell[i] : -1;
+  }
+#pragma unroll
+  for (int q = 0; q < KEYS_PER; ++q) {
+    const int64_t i = i0 + q * BIN_THREADS;
+    uint32_t k = nbins;
+    if (c[q] >= 0 && (uint32_t)c[q] < nbins) {
+      k = (uint32_t)c[q];
+      if (key_mode == DUST_BIN_TILE) {
+        // one box (the common case): its descriptor is uniform
+        if (nbox == 1) {
+          k = tile_key(boxes[0], c[q], ts);
+        } else {
+          const Box& B = boxes[find_box(boxes, nbox, c[q])];
+          k = tile_key(B, c[q] - B.cell_base, ts);
+        }
+      }
+    }
+    if (i < n) key[i] = k;
+  }
+}
+
+// The block of keys of a workgroup (see the head of the file).
+__device__ __forceinline__ uint32_t bin_block(uint32_t nblocks) {
+  const uint32_t xcd = blockIdx.x & 7u, per = nblocks >> 3, rem = nblocks & 7u;
+  return xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
+}
+
+// Digit histogram of every block of BIN_THREADS * ITEMS keys: hist[digit *
+// nblocks + block].  Only the first lane of a run of equal digits adds (keys
+// that are nearly sorted would queue on one counter).
+template <int NDIG, int ITEMS>
+__global__ void __launch_bounds__(BIN_THREADS)
+    k_digit_hist(const uint32_t* __restrict__ key, uint32_t n, int shift, int nbits, uint32_t* __restrict__ hist,
+                 uint32_t nblocks) {
+  __shared__ uint32_t h[NDIG];
+  const int t = threadIdx.x, lane = t & 63;
+  const uint32_t ndig = 1u << nbits, mask = ndig - 1;
+  const uint32_t b = bin_block(nblocks);
+  for (uint32_t d = t; d < ndig; d += BIN_THREADS) h[d] = 0;
+  __syncthreads();
+  const uint32_t base = b * (uint32_t)(BIN_THREADS * ITEMS);
+  uint32_t k[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const uint32_t l = c * BIN_THREADS + t;
+    k[c] = l < n - base ? key[base + l] : 0u;
+  }
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const bool valid = (uint32_t)(c * BIN_THREADS + t) < n - base;   // (valid lanes come first)
+    const uint32_t d = (k[c] >> shift) & mask;
+    const uint32_t prev = __shfl_up(d, 1);
+    const uint64_t all = __ballot(valid);
+    const uint64_t heads = __ballot(valid && (lane == 0 || d != prev));
+    if ((heads >> lane) & 1u) {
+      // lanes up to the next head, or the last valid one
+      const uint64_t above = lane == 63 ? 0ull : heads >> (lane + 1);
+      const uint32_t len = above ? (uint32_t)__ffsll((unsigned long long)above) : (uint32_t)__popcll(all) - lane;
+      atomicAdd(&h[d], len);
     }
   }
-  key[i] = k;
+  __syncthreads();
+  for (uint32_t d = t; d < ndig; d += BIN_THREADS) hist[(size_t)d * nblocks + b] = h[d];
 }
 
-__global__ void __launch_bounds__(BIN_THREADS) k_digit_hist(const uint32_t* key, int64_t n,
-                                                            int shift, uint32_t* hist,
-                                                            int nblocks) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * BIN_TILE;
-  for (int c = 0; c < BIN_ITEMS; ++c) {
-    int64_t e = base + c * BIN_THREADS + threadIdx.x;
-    if (e < n) atomicAdd(&h[(key[e] >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
-}
-
-// One radix pass of one block of BIN_TILE elements: the block's elements
-// are first placed in LDS in stable digit order (wave ballots rank lanes with
-// equal digits, LDS counters carry the ranks across waves and chunks), then
-// written out run by run, so that consecutive threads write consecutive
-// addresses of a digit's output range.  val_in = nullptr: values are the
-// element indices (first pass).
-__global__ void __launch_bounds__(BIN_THREADS) k_digit_scatter(const uint32_t* __restrict__ key_in,
-                                                               const uint32_t* __restrict__ val_in,
-                                                               int64_t n, int shift,
-                                                               const uint32_t* __restrict__ offs,
-                                                               int nblocks, uint32_t* key_out,
-                                                               uint32_t* val_out) {
-  __shared__ uint32_t s_key[BIN_TILE], s_val[BIN_TILE];
-  __shared__ uint32_t lstart[256], running[256], gstart[256];
-  __shared__ uint32_t cnt[BIN_THREADS / 64][256];
+// One radix pass of one block: every wave ranks its 64 * ITEMS consecutive
+// keys among its own (round by round of 64, ballots for lanes with equal
+// digits, counters of its own for the rounds), the counters of the waves
+// become places in stable digit order, the keys and then the values are put
+// there in LDS and written out run by run.  offs: the scanned histogram.
+// val_in = nullptr: values are the element indices (first pass).
+template <int NDIG, int ITEMS>
+__global__ void __launch_bounds__(BIN_THREADS)
+    k_digit_scatter(const uint32_t* __restrict__ key_in, const uint32_t* __restrict__ val_in, uint32_t n, int shift,
+                    int nbits, const uint32_t* __restrict__ offs, uint32_t nblocks, uint32_t* __restrict__ key_out,
+                    uint32_t* __restrict__ val_out) {
+  constexpr int KEYS = BIN_THREADS * ITEMS;
+  constexpr int P = NDIG / BIN_THREADS;   // digits of a thread
+  static_assert(KEYS < 65536 && NDIG % BIN_THREADS == 0 && NDIG <= (1 << BIN_MAX_BITS), "16-bit places");
+  __shared__ uint32_t stage[KEYS];
+  __shared__ uint32_t goff[NDIG];
+  __shared__ uint16_t cnt[BIN_WAVES][NDIG];
+  __shared__ uint32_t wsum[BIN_WAVES];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t base = (int64_t)blockIdx.x * BIN_TILE;
-  const int nloc = (int)(n - base < BIN_TILE ? n - base : BIN_TILE);
-  uint32_t k[BIN_ITEMS], v[BIN_ITEMS];
+  const uint32_t ndig = 1u << nbits, mask = ndig - 1;
+  const uint32_t b = bin_block(nblocks), base = b * (uint32_t)KEYS;
+  const int nloc = (int)(n - base < (uint32_t)KEYS ? n - base : (uint32_t)KEYS);
+  const int l0 = wv * 64 * ITEMS + lane;   // this lane's first key of the block
+  uint32_t k[ITEMS], v[ITEMS];
+  uint16_t r[ITEMS];
 #pragma unroll
-  for (int c = 0; c < BIN_ITEMS; ++c) {
-    const int l = c * BIN_THREADS + t;
-    const bool valid = l < nloc;
-    k[c] = valid ? key_in[base + l] : 0u;
-    v[c] = valid ? (val_in ? val_in[base + l] : (uint32_t)(base + l)) : 0u;
+  for (int c = 0; c < ITEMS; ++c) {
+    const int l = l0 + 64 * c;
+    k[c] = l < nloc ? key_in[base + l] : 0u;
   }
-  // block histogram of the digit, then its exclusive scan
-  running[t] = 0;
-  for (int w = 0; w < BIN_THREADS / 64; ++w) cnt[w][t] = 0;
-  gstart[t] = offs[(int64_t)t * nblocks + blockIdx.x];
-  __syncthreads();
 #pragma unroll
-  for (int c = 0; c < BIN_ITEMS; ++c)
-    if (c * BIN_THREADS + t < nloc) atomicAdd(&running[(k[c] >> shift) & 255u], 1u);
-  __syncthreads();
-  const uint32_t mine = running[t];
-  lstart[t] = mine;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const uint32_t x = t >= off ? lstart[t - off] : 0u;
-    __syncthreads();
-    lstart[t] += x;
-    __syncthreads();
+  for (int c = 0; c < ITEMS; ++c) {
+    const int l = l0 + 64 * c;
+    v[c] = l < nloc ? (val_in ? val_in[base + l] : base + l) : 0u;
   }
-  lstart[t] -= mine;
-  running[t] = lstart[t];
+  for (int d = t; d < BIN_WAVES * NDIG; d += BIN_THREADS) (&cnt[0][0])[d] = 0;
   __syncthreads();
-  // stable placement in LDS, chunk by chunk
-  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-  for (int c = 0; c < BIN_ITEMS; ++c) {
-    const bool valid = c * BIN_THREADS + t < nloc;
-    const uint32_t d = (k[c] >> shift) & 255u;
-    unsigned long long peers = __ballot(valid);
-    for (int bt = 0; bt < 8; ++bt) {
-      const unsigned long long m = __ballot((d >> bt) & 1u);
-      peers &= ((d >> bt) & 1u) ? m : ~m;
+  for (int c = 0; c < ITEMS; ++c) {
+    const bool valid = l0 + 64 * c < nloc;
+    const uint32_t d = (k[c] >> shift) & mask;
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int bt = 0; bt < BIN_MAX_BITS; ++bt) {
+      if (bt >= nbits) break;   // (uniform)
+      const bool one = (d >> bt) & 1u;
+      const uint64_t m = __ballot(one);
+      peers &= one ? m : ~m;
     }
     const uint32_t rank = (uint32_t)__popcll(peers & lt);
-    if (valid && rank == 0) cnt[wv][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = running[d] + rank;
-      for (int w = 0; w < wv; ++w) pos += cnt[w][d];
-      s_key[pos] = k[c];
-      s_val[pos] = v[c];
-    }
-    __syncthreads();
-    uint32_t add = 0;
-    for (int w = 0; w < BIN_THREADS / 64; ++w) {
-      add += cnt[w][t];
-      cnt[w][t] = 0;
-    }
-    running[t] += add;
-    __syncthreads();
+    const uint32_t old = cnt[wv][d];
+    if (valid && rank == 0) cnt[wv][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
+    r[c] = (uint16_t)(old + rank);
   }
-  // write out run by run
-  for (int p = t; p < nloc; p += BIN_THREADS) {
-    const uint32_t kk = s_key[p];
-    const uint32_t d = (kk >> shift) & 255u;
-    const uint32_t o = gstart[d] + (uint32_t)p - lstart[d];
-    key_out[o] = kk;
-    val_out[o] = s_val[p];
+  __syncthreads();
+  // places: exclusive scan over (digit, wave)
+  uint32_t tot[P], mine = 0;
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    tot[j] = 0;
+#pragma unroll
+    for (int w = 0; w < BIN_WAVES; ++w) tot[j] += cnt[w][t * P + j];
+    mine += tot[j];
+  }
+  uint32_t incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_up(incl, o);
+    if (lane >= o) incl += u;
+  }
+  if (lane == 63) wsum[wv] = incl;
+  __syncthreads();
+  uint32_t start = incl - mine;
+  for (int w = 0; w < wv; ++w) start += wsum[w];
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const uint32_t d = (uint32_t)(t * P + j);
+    // a place p of digit d goes to goff[d] + p
+    goff[d] = (d < ndig ? offs[(size_t)d * nblocks + b] : 0u) - start;
+    uint32_t q = start;
+#pragma unroll
+    for (int w = 0; w < BIN_WAVES; ++w) {
+      const uint32_t x = cnt[w][d];
+      cnt[w][d] = (uint16_t)q;
+      q += x;
+    }
+    start += tot[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    r[c] = (uint16_t)(cnt[wv][(k[c] >> shift) & mask] + r[c]);
+    if (l0 + 64 * c < nloc) stage[r[c]] = k[c];
+  }
+  __syncthreads();
+  // the keys run by run; where each went, for the values
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int p = c * BIN_THREADS + t;
+    const uint32_t kk = stage[p];   // (past nloc: not used)
+    const uint32_t o = goff[(kk >> shift) & mask] + (uint32_t)p;
+    if (p < nloc) key_out[o] = kk;
+    k[c] = o;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (l0 + 64 * c < nloc) stage[r[c]] = v[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int p = c * BIN_THREADS + t;
+    if (p < nloc) val_out[k[c]] = stage[p];
   }
 }
 
@@ -169,7 +258,35 @@ __global__ void k_scan_add(uint32_t* a, int64_t n, const uint32_t* block_offs) {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-int64_t bin_blocks(int64_t n) { return ceil_div(n, BIN_TILE); }
+// A sort's passes: ITEMS keys of a thread (few where the launch would not
+// fill the chip), and as few passes as the histogram's room allows.
+struct BinPlan {
+  int items, npass, nbits;   // nbits: of every pass but the last, which has the rest
+  int64_t nblocks;
+};
+static BinPlan bin_plan(int64_t n, int64_t nbins, size_t hist_words) {
+  int bits = 1;
+  while (bits < 32 && ((uint64_t)1 << bits) <= (uint64_t)nbins) ++bits;
+  BinPlan p{};
+  p.npass = (bits + BIN_MAX_BITS - 1) / BIN_MAX_BITS;
+  p.items = n >= BIN_FEW ? 16 : 4;
+  for (;;) {
+    p.nbits = (bits + p.npass - 1) / p.npass;
+    p.nblocks = ceil_div(n, BIN_THREADS * p.items);
+    if (((size_t)p.nblocks << p.nbits) <= hist_words) return p;
+    if (p.items == 4) p.items = 16;   // larger blocks, then digits of 8 bits: these always fit
+    else ++p.npass;
+  }
+}
+
+// Room of the histogram for n keys: the largest digits in the blocks that
+// bin_plan takes (fixed: the least that a sort needs, 8-bit digits in blocks
+// of 4096).
+size_t bin_hist_words(int64_t n, bool fixed) {
+  const size_t least = (size_t)256 * ceil_div(n, BIN_THREADS * 16);
+  if (fixed) return least;
+  return std::max(least, (size_t)ceil_div(n, BIN_THREADS * (n >= BIN_FEW ? 16 : 4)) << BIN_MAX_BITS);
+}
 
 size_t bin_scan_tmp_words(int64_t m) {
   size_t words = 0;
@@ -222,21 +339,30 @@ int launch_bin(const int32_t* cell, int64_t n, const Box* boxes_dev, int nbox, i
     return 0;
   }
   if (!keys_ready)
-    hipLaunchKernelGGL(k_make_keys, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, cell, n,
-                       boxes_dev, nbox, (uint32_t)nbins, key_mode, tile, w.key[0]);
+    hipLaunchKernelGGL(k_make_keys, dim3((unsigned)ceil_div(n, BIN_THREADS * KEYS_PER)), dim3(BIN_THREADS), 0, st,
+                       cell, n, boxes_dev, nbox, (uint32_t)nbins, key_mode, tile, w.key[0]);
+  const BinPlan plan = bin_plan(n, nbins, w.hist_words);
   int bits = 1;
   while (bits < 32 && ((uint64_t)1 << bits) <= (uint64_t)nbins) ++bits;
-  int npass = (bits + 7) / 8;
-  int nblocks = (int)ceil_div(n, BIN_TILE);
+  const dim3 grid((unsigned)plan.nblocks), block(BIN_THREADS);
   int cur = 0;
-  for (int p = 0; p < npass; ++p) {
-    int shift = 8 * p;
-    hipLaunchKernelGGL(k_digit_hist, dim3(nblocks), dim3(BIN_THREADS), 0, st, w.key[cur], n, shift,
-                       w.hist, nblocks);
-    scan_exclusive(w.hist, (int64_t)256 * nblocks, w.scan_tmp, st);
-    hipLaunchKernelGGL(k_digit_scatter, dim3(nblocks), dim3(BIN_THREADS), 0, st, w.key[cur],
-                       p == 0 ? (const uint32_t*)nullptr : (const uint32_t*)w.val[cur], n, shift,
-                       w.hist, nblocks, w.key[1 - cur], w.val[1 - cur]);
+  for (int p = 0; p < plan.npass; ++p) {
+    const int shift = p * plan.nbits, nb = std::min(plan.nbits, bits - shift);
+    const uint32_t* vin = p == 0 ? nullptr : w.val[cur];
+    auto pass = [&](auto hist_kern, auto scatter_kern) {
+      hipLaunchKernelGGL(hist_kern, grid, block, 0, st, (const uint32_t*)w.key[cur], (uint32_t)n, shift, nb, w.hist,
+                         (uint32_t)plan.nblocks);
+      scan_exclusive(w.hist, (int64_t)plan.nblocks << nb, w.scan_tmp, st);
+      hipLaunchKernelGGL(scatter_kern, grid, block, 0, st, (const uint32_t*)w.key[cur], vin, (uint32_t)n, shift, nb,
+                         (const uint32_t*)w.hist, (uint32_t)plan.nblocks, w.key[1 - cur], w.val[1 - cur]);
+    };
+    if (plan.nbits <= 8) {
+      if (plan.items == 4) pass(k_digit_hist<256, 4>, k_digit_scatter<256, 4>);
+      else pass(k_digit_hist<256, 16>, k_digit_scatter<256, 16>);
+    } else {
+      if (plan.items == 4) pass(k_digit_hist<512, 4>, k_digit_scatter<512, 4>);
+      else pass(k_digit_hist<512, 16>, k_digit_scatter<512, 16>);
+    }
     cur = 1 - cur;
   }
   if (perm_out)

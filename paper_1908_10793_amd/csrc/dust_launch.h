@@ -107,13 +107,16 @@ template <typename TS> void launch_clear_deposits(const FView<TS>& fl, int nch, 
 struct BinWork {
   uint32_t *key[2];
   uint32_t *val[2];
-  uint32_t *hist;       // 256 * nblocks, scanned in place
+  uint32_t *hist;       // digits * blocks, scanned in place
+  size_t hist_words;    // its room
   uint32_t *scan_tmp;   // block sums of the scans
   void *gather_tmp;     // 8 bytes per particle (permutation application)
   size_t cap_n;
 };
 size_t bin_scan_tmp_words(int64_t n);
-int64_t bin_blocks(int64_t n);   // radix-pass blocks for n keys (digit histogram columns)
+// Words of the histogram for n keys; fixed: the least that a sort needs (of
+// more digits per pass it then takes as many as fit).
+size_t bin_hist_words(int64_t n, bool fixed);
 struct TileShape { int32_t t[3]; };
 // Stable sort of particles by key; writes perm (sorted slot -> input index)
 // and bin_start (nbins+1) if given.  key_mode: DUST_BIN_CELL or DUST_BIN_TILE;
