@@ -610,6 +610,16 @@ void run_push(Ctx* c, const PView<TS>& pv, const Forces& F, double dt, int phase
     launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dg, st);
 }
 
+// After a step's particles: grid sums, fold, feedback, and the end of the step.
+template <typename TS>
+void end_step(Ctx* c, const FView<TS>& fv, const Forces& F, double dt, int flags, hipStream_t st) {
+  DiagDev* dg = (flags & DUST_STEP_DIAG) ? c->diag : nullptr;
+  StepEnd end{c->grid_part, 0, dg, c->tdev, dt};
+  if (dg) end.nparts = launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, st);
+  launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, flags & DUST_STEP_APPLY_FEEDBACK, st);
+  launch_finish<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, &end, st);
+}
+
 // One unfused step (time in c->tdev[0] at the start of the step).
 template <typename TS, typename A>
 void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces& F, double dt,
@@ -624,9 +634,8 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
   for (int k = nc + 1; k < 4; ++k) imp[k] = nullptr;
   DiagDev* dg = (flags & DUST_STEP_DIAG) ? c->diag : nullptr;
   DiagDev* dflags = c->diag;  // sticky flags always recorded
-  if (!(flags & DUST_STEP_NO_FILL))
-    launch_fill<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, c->xg, st);
-  launch_clear_deposits<TS>(fv, nc + 1, c->n_stored, st);
+  launch_prepare<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, !(flags & DUST_STEP_NO_FILL),
+                     c->xg, nc + 1, c->n_stored, st);
   const double* xg = (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg;
   if (c->step_sorted) {
     if constexpr (std::is_same<A, double>::value) {
@@ -651,11 +660,7 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
       launch_deposit<TS, A, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fv, cimp, dflags, st);
     launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dflags, st);
   }
-  if (dg)
-    launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, st);
-  launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, st);
-  if (flags & DUST_STEP_APPLY_FEEDBACK)
-    launch_feedback<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, st);
+  end_step<TS>(c, fv, F, dt, flags, st);
 }
 
 // Whether a fused step runs the FP32 uniform-Cartesian tile kernel
@@ -719,9 +724,8 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
     mv.clear_removed = c->shadow_new;
     c->shadow_new = false;
   }
-  if (!(flags & DUST_STEP_NO_FILL))
-    launch_fill<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, c->xg, st);
-  launch_clear_deposits<TS>(fv, nc + 1, c->n_stored, st);
+  launch_prepare<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, !(flags & DUST_STEP_NO_FILL),
+                     c->xg, nc + 1, c->n_stored, st);
   const bool prof = c->prof_used < c->prof_max;
   hipEvent_t ev0 = prof ? c->prof_ev[2 * c->prof_used] : nullptr;
   hipEvent_t ev1 = prof ? c->prof_ev[2 * c->prof_used + 1] : nullptr;
@@ -737,11 +741,7 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
                         (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr, ev0, ev1, st);
   HIP_TRY(hipGetLastError());
   if (prof) ++c->prof_used;
-  if (dg)
-    launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, st);
-  launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, st);
-  if (flags & DUST_STEP_APPLY_FEEDBACK)
-    launch_feedback<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, st);
+  end_step<TS>(c, fv, F, dt, flags, st);
   return DUST_OK;
 }
 
@@ -757,7 +757,6 @@ dust_status_t run_steps(Ctx* c, dust_particles_t* p, dust_fields_t* f, double dt
       // the unfused chain passes gathered velocities and impulses through
       // memory, where FP32 would lose the slip: it computes in FP64
       unfused_step<TS, double>(c, pv, fv, F, dt, flags, st);
-      launch_advance_time(c->tdev, dt, (flags & DUST_STEP_DIAG) ? c->diag : nullptr, st);
     }
     return DUST_OK;
   }
@@ -765,7 +764,6 @@ dust_status_t run_steps(Ctx* c, dust_particles_t* p, dust_fields_t* f, double dt
   for (int s = 0; s < nsteps; ++s) {
     dust_status_t e = fused_step<TS, A>(c, pv, s % rebin_every == 0 ? sh : none, fv, F, dt, flags, st);
     if (e) return e;
-    launch_advance_time(c->tdev, dt, (flags & DUST_STEP_DIAG) ? c->diag : nullptr, st);
   }
   constexpr bool f32 = std::is_same<TS, float>::value && std::is_same<A, float>::value;
   c->lay_valid = use_c3(c, f32, F, pv);
@@ -1107,7 +1105,7 @@ dust_status_t dust_fill_ghosts(void* ctx, dust_fields_t* f, const dust_forces_t*
   return dispatch(c, [&](auto ts, auto) -> dust_status_t {
     using TS = decltype(ts);
     FView<TS> fv = fview<TS>(f);
-    launch_fill<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.0, fv, c->xg, st);
+    launch_prepare<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.0, fv, true, c->xg, 0, 0, st);
     HIP_TRY(hipGetLastError());
     return DUST_OK;
   });
@@ -1127,7 +1125,8 @@ dust_status_t dust_fold_ghosts(void* ctx, dust_fields_t* f, const dust_forces_t*
   return dispatch(c, [&](auto ts, auto) -> dust_status_t {
     using TS = decltype(ts);
     FView<TS> fv = fview<TS>(f);
-    launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.0, fv, st);
+    launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.0, fv, false, st);
+    launch_finish<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, nullptr, st);
     HIP_TRY(hipGetLastError());
     return DUST_OK;
   });

@@ -773,226 +773,201 @@ __device__ __forceinline__ int64_t grid_thread(const BoxGrid& g, int e) {
   return (int64_t)(blockIdx.x - g.blk0[e]) * blockDim.x + threadIdx.x;
 }
 
-// x ghosts of one box: shear-periodic (interpolated in y) or periodic.
-template <typename TS>
-__global__ void k_fill_x(const Box* boxes, BoxGrid bg, Arr4<TS> arrs, int boost, double qOmega,
-                         const double* tdev, double toff) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  const int shear = B.ax[0].bc_lo == BC_SHEAR;
-  const int vy_slot = B.geom == GEOM_CART && boost ? 2 : -1;
-  TS* a = arrs.a[blockIdx.y];
-  const int comp_vy = (int)blockIdx.y == vy_slot;
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)n1 * n2) return;
-  const Shift sh = make_shift(B, qOmega, *tdev + toff);
-  int j = (int)(t % n1), k = (int)(t / n1);
-  if (shear) {
-    // right ghost (x_0 + L, y_j) = (x_0, y_j + s); left ghost = (x_{n-1}, y_j - s)
-    int jl = j + sh.si;
-    double fr = sh.sf;
-    int j0 = ((jl % n1) + n1) % n1, j1 = ((jl + 1) % n1 + n1) % n1;
-    double v = (1.0 - fr) * double(a[stored_index(B, 0, j0, k)]) +
-               fr * double(a[stored_index(B, 0, j1, k)]);
-    a[stored_index(B, n0, j, k)] = TS(v - (comp_vy ? sh.u : 0.0));
-    double pos_fl = -sh.si - (sh.sf > 0 ? 1 : 0);
-    int jm = j + (int)pos_fl;
-    double frm = sh.sf > 0 ? 1.0 - sh.sf : 0.0;
-    j0 = ((jm % n1) + n1) % n1;
-    j1 = ((jm + 1) % n1 + n1) % n1;
-    v = (1.0 - frm) * double(a[stored_index(B, n0 - 1, j0, k)]) +
-        frm * double(a[stored_index(B, n0 - 1, j1, k)]);
-    a[stored_index(B, -1, j, k)] = TS(v + (comp_vy ? sh.u : 0.0));
+// The ghost cells of a box that boundary conditions fill or fold, in disjoint
+// sets: z ghosts (all i, j), y ghosts (all i, active k), x ghosts (active j
+// and k), of the axes whose faces are not open.
+struct GhostSet {
+  int n0, n1, n2, g0, g1;   // active cells; stored extents
+  bool x, y, z;             // the axis has filled ghosts
+  int64_t cx, cy, cz;       // cells of each set
+};
+__device__ __forceinline__ GhostSet ghost_set(const Box& B) {
+  GhostSet s;
+  s.n0 = B.ax[0].n;
+  s.n1 = B.ax[1].n;
+  s.n2 = B.ndim > 2 ? B.ax[2].n : 1;
+  s.g0 = s.n0 + 2;
+  s.g1 = s.n1 + 2;
+  s.x = B.ax[0].bc_lo != BC_OPEN;
+  s.y = B.ax[1].bc_lo == BC_PERIODIC;
+  s.z = B.ndim > 2 && B.ax[2].bc_lo == BC_PERIODIC;
+  s.cx = s.x ? 2 * (int64_t)s.n1 * s.n2 : 0;
+  s.cy = s.y ? 2 * (int64_t)s.g0 * s.n2 : 0;
+  s.cz = s.z ? 2 * (int64_t)s.g0 * s.g1 : 0;
+  return s;
+}
+// t-th of them (t < cx + cy + cz), both sides of a face cell in turn last.
+__device__ __forceinline__ void ghost_cell(const GhostSet& s, int64_t t, int& i, int& j, int& k) {
+  if (t < s.cx) {
+    const uint32_t half = (uint32_t)(s.cx / 2), u = (uint32_t)t, v = u < half ? u : u - half;
+    i = u < half ? -1 : s.n0;
+    k = (int)(v / (uint32_t)s.n1);
+    j = (int)(v - (uint32_t)k * s.n1);
+  } else if ((t -= s.cx) < s.cy) {
+    const uint32_t half = (uint32_t)(s.cy / 2), u = (uint32_t)t, v = u < half ? u : u - half;
+    j = u < half ? -1 : s.n1;
+    k = (int)(v / (uint32_t)s.g0);
+    i = (int)(v - (uint32_t)k * s.g0) - 1;
   } else {
-    a[stored_index(B, -1, j, k)] = a[stored_index(B, n0 - 1, j, k)];
-    a[stored_index(B, n0, j, k)] = a[stored_index(B, 0, j, k)];
+    const uint32_t half = (uint32_t)(s.cz / 2), u = (uint32_t)(t - s.cy), v = u < half ? u : u - half;
+    k = u < half ? -1 : s.n2;
+    const int q = (int)(v / (uint32_t)s.g0);
+    i = (int)(v - (uint32_t)q * s.g0) - 1;
+    j = q - 1;
   }
 }
 
-// FP64 copy of the shear-periodic x-ghost gas of velocity component m, with
-// the y and z ghost rows of the layer (periodic images): the interpolated and
-// boosted ghost values keep their FP64 rounding, so that a particle next to
-// the shear boundary sees the gas at the accuracy of the interior values.
+// Shear-periodic x-ghost value of the row (j, k) of a field, FP64: the other
+// face's active cells, interpolated in y.  (side 0: the ghost below x_lo,
+// (x_{n-1}, y_j - s); 1: above x_hi, (x_0, y_j + s); dv: the boost of v_y.)
 template <typename TS>
-__global__ void k_fill_xghost(const Box* boxes, BoxGrid bg, Arr4<TS> vel, double* xg, double qOmega,
-                              const double* tdev, double toff, int boost) {
-  const int ge = grid_entry(bg);
-  const Box& B = boxes[bg.box[ge]];
-  const int m = blockIdx.y, comp_vy = boost && m == 1;
-  const TS* a = vel.a[m];
-  const int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ax[2].n;
-  const int g1 = n1 + 2, g2 = n2 + 2;
-  const int64_t t = grid_thread(bg, ge);
-  if (t >= (int64_t)g1 * g2) return;
-  const Shift sh = make_shift(B, qOmega, *tdev + toff);
-  const int jg = (int)(t % g1), kg = (int)(t / g1);
-  const int j = ((jg - 1) % n1 + n1) % n1, k = ((kg - 1) % n2 + n2) % n2;
-  int jl = j + sh.si;
-  int j0 = ((jl % n1) + n1) % n1, j1 = ((jl + 1) % n1 + n1) % n1;
-  double right = (1.0 - sh.sf) * double(a[stored_index(B, 0, j0, k)]) +
-                 sh.sf * double(a[stored_index(B, 0, j1, k)]) - (comp_vy ? sh.u : 0.0);
-  int jm = j - sh.si - (sh.sf > 0 ? 1 : 0);
-  double frm = sh.sf > 0 ? 1.0 - sh.sf : 0.0;
-  j0 = ((jm % n1) + n1) % n1;
-  j1 = ((jm + 1) % n1 + n1) % n1;
-  double left = (1.0 - frm) * double(a[stored_index(B, n0 - 1, j0, k)]) +
-                frm * double(a[stored_index(B, n0 - 1, j1, k)]) + (comp_vy ? sh.u : 0.0);
-  const int64_t layer = (int64_t)g1 * g2;
-  xg[B.xg_base + (0 * 3 + m) * layer + t] = left;
-  xg[B.xg_base + (1 * 3 + m) * layer + t] = right;
+__device__ __forceinline__ double shear_ghost(const Box& B, const TS* a, const Shift& sh, int side, int j, int k,
+                                              double dv) {
+  const int n0 = B.ax[0].n, n1 = B.ax[1].n;
+  const int jl = side ? j + sh.si : j - sh.si - (sh.sf > 0 ? 1 : 0);
+  const double fr = side ? sh.sf : (sh.sf > 0 ? 1.0 - sh.sf : 0.0);
+  const int i = side ? 0 : n0 - 1;
+  const int j0 = ((jl % n1) + n1) % n1, j1 = ((jl + 1) % n1 + n1) % n1;
+  const double v = (1.0 - fr) * double(a[stored_index(B, i, j0, k)]) + fr * double(a[stored_index(B, i, j1, k)]);
+  return side ? v - dv : v + dv;
 }
 
-template <typename TS> __global__ void k_fill_y(const Box* boxes, BoxGrid bg, Arr4<TS> arrs) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  TS* a = arrs.a[blockIdx.y];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)(n0 + 2) * n2) return;
-  int i = (int)(t % (n0 + 2)) - 1, k = (int)(t / (n0 + 2));
-  a[stored_index(B, i, -1, k)] = a[stored_index(B, i, n1 - 1, k)];
-  a[stored_index(B, i, n1, k)] = a[stored_index(B, i, 0, k)];
+// What one step needs of the grid before its particles, in one launch (each
+// of the five it replaces took 4 to 5 us on a small grid, whatever its work):
+// the gas ghosts, the FP64 x-ghost gas of shear-periodic boxes, and cleared
+// deposits.  A ghost cell takes its value from active cells directly: an
+// image in z of an image in y of a row of the other x face is computed from
+// that face, so no order among the ghosts is needed.
+//
+// Blocks of an entry: ghosts of rho and every velocity component, then the
+// x-ghost layer of every component; past the last entry: deposits.
+static constexpr int CLEAR_PER = 4;   // deposits that a thread clears
+template <typename TS> struct Prepare {
+  Arr4<TS> gas;        // rho, velocity components
+  int na;              // arrays (0: no ghosts)
+  double* xg;          // FP64 x-ghost layers, or null
+  double qOmega, toff;
+  const double* tdev;
+  int boost;
+  Arr4<TS> dep;        // to clear
+  int nch;
+  int64_t n;
+};
+__host__ __device__ __forceinline__ int64_t fill_cells(const Box& B) {
+  const int64_t n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
+  return (B.ax[0].bc_lo != BC_OPEN ? 2 * n1 * n2 : 0) + (B.ax[1].bc_lo == BC_PERIODIC ? 2 * (n0 + 2) * n2 : 0) +
+         (B.ndim > 2 && B.ax[2].bc_lo == BC_PERIODIC ? 2 * (n0 + 2) * (n1 + 2) : 0);
 }
-
-template <typename TS> __global__ void k_fill_z(const Box* boxes, BoxGrid bg, Arr4<TS> arrs) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  TS* a = arrs.a[blockIdx.y];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ax[2].n;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)(n0 + 2) * (n1 + 2)) return;
-  int i = (int)(t % (n0 + 2)) - 1, j = (int)(t / (n0 + 2)) - 1;
-  a[stored_index(B, i, j, -1)] = a[stored_index(B, i, j, n2 - 1)];
-  a[stored_index(B, i, j, n2)] = a[stored_index(B, i, j, 0)];
+__host__ __device__ __forceinline__ int64_t xghost_cells(const Box& B) {
+  return B.xg_base >= 0 ? (int64_t)(B.ax[1].n + 2) * (B.ax[2].n + 2) : 0;
 }
+__host__ __device__ __forceinline__ uint32_t blocks256(int64_t n) { return (uint32_t)((n + 255) / 256); }
 
-template <typename TS> __global__ void k_fold_z(const Box* boxes, BoxGrid bg, Arr4<TS> arrs) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  TS* a = arrs.a[blockIdx.y];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ax[2].n;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)(n0 + 2) * (n1 + 2)) return;
-  int i = (int)(t % (n0 + 2)) - 1, j = (int)(t / (n0 + 2)) - 1;
-  int64_t gl = stored_index(B, i, j, -1), gh = stored_index(B, i, j, n2);
-  a[stored_index(B, i, j, n2 - 1)] += a[gl];
-  a[stored_index(B, i, j, 0)] += a[gh];
-  a[gl] = TS(0);
-  a[gh] = TS(0);
-}
-
-template <typename TS> __global__ void k_fold_y(const Box* boxes, BoxGrid bg, Arr4<TS> arrs) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  TS* a = arrs.a[blockIdx.y];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)(n0 + 2) * n2) return;
-  int i = (int)(t % (n0 + 2)) - 1, k = (int)(t / (n0 + 2));
-  int64_t gl = stored_index(B, i, -1, k), gh = stored_index(B, i, n1, k);
-  a[stored_index(B, i, n1 - 1, k)] += a[gl];
-  a[stored_index(B, i, 0, k)] += a[gh];
-  a[gl] = TS(0);
-  a[gh] = TS(0);
-}
-
-// x fold, written as a gather over the ghost rows that feed each partner
-// cell (no atomics).  The energy channel (e != NULL) gains +/- u D_y.
-template <typename TS>
-__global__ void k_fold_x(const Box* boxes, BoxGrid bg, Arr4<TS> arrs, const TS* dy, int boost_energy,
-                         double qOmega, const double* tdev, double toff) {
-  const int ge = grid_entry(bg);
-  const Box& B = boxes[bg.box[ge]];
-  const int shear = B.ax[0].bc_lo == BC_SHEAR;
-  const int nch = B.geom == GEOM_CART ? B.ndim : 3;
-  const int energy_slot = shear && boost_energy ? nch : -1;
-  TS* a = arrs.a[blockIdx.y];
-  const int is_energy = (int)blockIdx.y == energy_slot;
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, ge);
-  if (t >= (int64_t)n1 * n2) return;
-  const Shift sh = make_shift(B, qOmega, *tdev + toff);
-  int jt = (int)(t % n1), k = (int)(t / n1);
-  auto wrapj = [n1](int j) { return ((j % n1) + n1) % n1; };
-  if (!shear) {
-    a[stored_index(B, n0 - 1, jt, k)] += a[stored_index(B, -1, jt, k)];
-    a[stored_index(B, 0, jt, k)] += a[stored_index(B, n0, jt, k)];
+template <typename TS> __global__ void __launch_bounds__(256) k_prepare(const Box* boxes, BoxGrid bg, Prepare<TS> pr) {
+  if (blockIdx.x >= bg.blk0[bg.n]) {
+    const uint32_t q = blockIdx.x - bg.blk0[bg.n], per = blocks256((pr.n + CLEAR_PER - 1) / CLEAR_PER);
+    const uint32_t ch = q / per;
+    TS* a = pr.dep.a[ch];
+    const int64_t i0 = (int64_t)(q - ch * per) * (256 * CLEAR_PER) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < CLEAR_PER; ++u)
+      if (i0 + u * 256 < pr.n) a[i0 + u * 256] = TS(0);
     return;
   }
-  auto gr = [&](int j) {  // right ghost value, energy frame-shifted
-    double v = double(a[stored_index(B, n0, j, k)]);
-    if (is_energy) v += sh.u * double(dy[stored_index(B, n0, j, k)]);
-    return v;
-  };
-  auto gl = [&](int j) {
-    double v = double(a[stored_index(B, -1, j, k)]);
-    if (is_energy) v -= sh.u * double(dy[stored_index(B, -1, j, k)]);
-    return v;
-  };
-  // right ghost row j lands on floor(j + s) (1 - sf) and floor(j + s) + 1 (sf)
-  double add0 = (1.0 - sh.sf) * gr(wrapj(jt - sh.si));
-  if (sh.sf > 0) add0 += sh.sf * gr(wrapj(jt - sh.si - 1));
-  // left ghost row j lands on floor(j - s) and floor(j - s) + 1
-  double addn;
-  if (sh.sf > 0) {
-    int c = sh.si + 1;  // ceil(s)
-    addn = sh.sf * gl(wrapj(jt + c)) + (1.0 - sh.sf) * gl(wrapj(jt + c - 1));
-  } else {
-    addn = gl(wrapj(jt + sh.si));
+  const int e = grid_entry(bg);
+  const Box& B = boxes[bg.box[e]];
+  const uint32_t bf = blocks256(fill_cells(B));
+  uint32_t q = blockIdx.x - bg.blk0[e];
+  if (q < bf * (uint32_t)pr.na) {
+    const int m = (int)(q / bf);
+    const int64_t t = (int64_t)(q - (uint32_t)m * bf) * 256 + threadIdx.x;
+    const GhostSet s = ghost_set(B);
+    if (t >= s.cx + s.cy + s.cz) return;
+    int i, j, k;
+    ghost_cell(s, t, i, j, k);
+    TS* a = pr.gas.a[m];
+    const int64_t to = stored_index(B, i, j, k);
+    if (s.z) k = k < 0 ? s.n2 - 1 : k >= s.n2 ? 0 : k;
+    if (s.y) j = j < 0 ? s.n1 - 1 : j >= s.n1 ? 0 : j;
+    // (an x ghost in a ghost row of an open y face is filled by nobody)
+    const bool xgh = s.x && (i < 0 || i >= s.n0) && j >= 0 && j < s.n1;
+    TS v;
+    if (xgh && B.ax[0].bc_lo == BC_SHEAR) {
+      const Shift sh = make_shift(B, pr.qOmega, *pr.tdev + pr.toff);
+      v = TS(shear_ghost(B, a, sh, i < 0 ? 0 : 1, j, k, B.geom == GEOM_CART && pr.boost && m == 2 ? sh.u : 0.0));
+    } else {
+      if (xgh) i = i < 0 ? s.n0 - 1 : 0;
+      v = a[stored_index(B, i, j, k)];
+    }
+    a[to] = v;
+    return;
   }
-  a[stored_index(B, 0, jt, k)] += TS(add0);
-  a[stored_index(B, n0 - 1, jt, k)] += TS(addn);
+  // FP64 copy of the shear-periodic x-ghost gas of velocity component m, with
+  // the y and z ghost rows of the layer (periodic images): the interpolated
+  // and boosted ghost values keep their FP64 rounding, so that a particle next
+  // to the shear boundary sees the gas at the accuracy of the interior values.
+  q -= bf * (uint32_t)pr.na;
+  const int64_t layer = xghost_cells(B);
+  const uint32_t bx = blocks256(layer);
+  const int m = (int)(q / bx);
+  const int64_t t = (int64_t)(q - (uint32_t)m * bx) * 256 + threadIdx.x;
+  if (t >= layer) return;
+  const int n1 = B.ax[1].n, n2 = B.ax[2].n, g1 = n1 + 2;
+  const Shift sh = make_shift(B, pr.qOmega, *pr.tdev + pr.toff);
+  const int jg = (int)(t % g1), kg = (int)(t / g1);
+  const int j = ((jg - 1) % n1 + n1) % n1, k = ((kg - 1) % n2 + n2) % n2;
+  const double dv = pr.boost && m == 1 ? sh.u : 0.0;
+#pragma unroll
+  for (int side = 0; side < 2; ++side)
+    pr.xg[B.xg_base + (side * 3 + m) * layer + t] = shear_ghost(B, pr.gas.a[m + 1], sh, side, j, k, dv);
 }
 
-template <typename TS> __global__ void k_clear_x_ghosts(const Box* boxes, BoxGrid bg, Arr4<TS> arrs) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  TS* a = arrs.a[blockIdx.y];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)n1 * n2) return;
-  int j = (int)(t % n1), k = (int)(t / n1);
-  a[stored_index(B, -1, j, k)] = TS(0);
-  a[stored_index(B, n0, j, k)] = TS(0);
+// Deposits of the ghost cells added to the active cells they are images of,
+// written as a gather (each active cell next to a face reads the ghosts that
+// feed it: those in z, then those in y with their own in z, then those in x
+// with theirs, in this order of additions), so that one launch folds every
+// axis; the ghosts are cleared by k_finish.  The energy channel of a
+// shear-periodic box gains -/+ u D_y across x.  With FEED, v_c += D_c / (rho
+// s_c) on every active cell with the folded deposits (read once).
+// Targets: the cells next to a face, of the active cells of the folded axes
+// and the stored cells of the others, in the first blocks of an entry; with
+// FEED the other active cells follow, in blocks of their own (folding in the
+// kernel's plain path took 81 us for a 128^3 FP32 shearing box; 35 so, as the
+// feedback alone, with its FP64 division per cell).
+struct FoldSet {
+  int n[3], lo[3], T[3];   // active cells; first target; targets
+  bool f[3];
+  int64_t c[3];            // targets next to a z, y (of the rest), x face
+};
+__host__ __device__ __forceinline__ FoldSet fold_set(const Box& B) {
+  FoldSet s;
+  for (int d = 0; d < 3; ++d) {
+    const bool ax = d < B.ndim;
+    s.n[d] = ax ? B.ax[d].n : 1;
+    s.f[d] = ax && (d == 0 ? B.ax[0].bc_lo != BC_OPEN : B.ax[d].bc_lo == BC_PERIODIC);
+    s.lo[d] = ax && !s.f[d] ? -1 : 0;
+  }
+  // (an x ghost in a ghost row of an open y face keeps what z folds into it)
+  if (s.f[2] && !s.f[1]) s.lo[0] = -1;
+  for (int d = 0; d < 3; ++d) s.T[d] = s.n[d] - 2 * s.lo[d];
+  const int64_t m0 = s.f[0] ? (s.n[0] > 1 ? 2 : 1) : 0, m1 = s.f[1] ? (s.n[1] > 1 ? 2 : 1) : 0,
+                m2 = s.f[2] ? (s.n[2] > 1 ? 2 : 1) : 0;
+  s.c[2] = m2 * s.T[0] * s.T[1];
+  s.c[1] = m1 * s.T[0] * (s.T[2] - m2);
+  s.c[0] = m0 * (s.T[1] - m1) * (s.T[2] - m2);
+  return s;
 }
 
-// Step start time (set, or advanced by dt), and the diagnostics' step count
-// when dg is given (one launch per step).
-__global__ void k_set_time(double* t, double v, double add, DiagDev* dg) {
-  t[0] = add != 0.0 ? t[0] + add : v;
-  if (dg) dg->steps += 1;
-}
+template <typename TS> struct Fold {
+  double qOmega, toff;
+  const double* tdev;
+  int boost_energy;
+};
 
-void launch_set_time(double* tdev, double v, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_time, dim3(1), dim3(1), 0, st, tdev, v, 0.0, (DiagDev*)nullptr);
-}
-void launch_advance_time(double* tdev, double dt, DiagDev* count, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_time, dim3(1), dim3(1), 0, st, tdev, 0.0, dt, count);
-}
-
-template <typename TS> __global__ void k_fill_values(Arr4<TS> arrs, int64_t n, TS v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) arrs.a[blockIdx.y][i] = v;
-}
-
-template <typename TS> __global__ void k_fill_value(TS* a, int64_t n, TS v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = v;
-}
-
-// v_c += D_c / (rho s_c) on the active cells of the boxes.
-template <typename TS> __global__ void k_feedback(const Box* boxes, BoxGrid bg, FView<TS> fl) {
-  const int e = grid_entry(bg);
-  const Box& B = boxes[bg.box[e]];
-  int n0 = B.ax[0].n, n1 = B.ax[1].n, n2 = B.ndim > 2 ? B.ax[2].n : 1;
-  int64_t t = grid_thread(bg, e);
-  if (t >= (int64_t)n0 * n1 * n2) return;
-  int idx[3];
-  unravel(B, t, idx);   // (active cell counts are below 2^31)
-  const int i = idx[0], j = idx[1], k = idx[2];
-  int64_t id = stored_index(B, i, j, k);
-  const int nc = B.geom == GEOM_CART ? B.ndim : 3;
+// v_c += D_c / (rho s_c) on an active cell.
+template <typename TS>
+__device__ __forceinline__ void feedback(const Box& B, const FView<TS>& fl, int nc, int i, int j, int64_t id,
+                                         const double* D) {
   double sc[3] = {1.0, 1.0, 1.0};
   if (B.geom != GEOM_CART) {
     double x0 = cell_centre<double, false>(B.ax[0], i);
@@ -1000,10 +975,153 @@ template <typename TS> __global__ void k_feedback(const Box* boxes, BoxGrid bg, 
     if (B.geom == GEOM_SPH) sc[2] = x0 * sin(cell_centre<double, false>(B.ax[1], j));
   }
   const double irho = 1.0 / double(fl.rho[id]);   // one division per cell
-  for (int c = 0; c < nc; ++c) {
-    const double q = double(fl.dep[c][id]) * irho;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (c >= nc) break;
+    const double q = D[c] * irho;
     fl.vel[c][id] = TS(double(fl.vel[c][id]) + (c == 0 ? q : q / sc[c]));
   }
+}
+
+template <typename TS, bool FOLD, bool FEED>
+__global__ void __launch_bounds__(256) k_fold(const Box* boxes, BoxGrid bg, FView<TS> fl, Fold<TS> fo) {
+  const int e = grid_entry(bg);
+  const Box& B = boxes[bg.box[e]];
+  int64_t t = grid_thread(bg, e);
+  FoldSet s{};
+  uint32_t be = 0;   // blocks of cells next to a face
+  if constexpr (FOLD) {
+    s = fold_set(B);
+    be = blocks256(s.c[0] + s.c[1] + s.c[2]);
+  }
+  const int nc = B.geom == GEOM_CART ? B.ndim : 3;
+  if (FEED && blockIdx.x - bg.blk0[e] >= be) {
+    t -= (int64_t)be * 256;
+    if (t >= B.ncell) return;
+    int idx[3];
+    unravel(B, t, idx);   // (active cell counts are below 2^31)
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (s.f[d] && (idx[d] == 0 || idx[d] == s.n[d] - 1)) return;
+    const int64_t id = stored_index(B, idx[0], idx[1], idx[2]);
+    double D[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) D[c] = c < nc ? double(fl.dep[c][id]) : 0.0;
+    feedback(B, fl, nc, idx[0], idx[1], id, D);
+    return;
+  }
+  if constexpr (!FOLD) return;
+  int i, j, k;
+  {
+    const int m1 = s.f[1] ? (s.n[1] > 1 ? 2 : 1) : 0, m2 = s.f[2] ? (s.n[2] > 1 ? 2 : 1) : 0;
+    // rows past the faces that are taken already
+    const int r1 = s.T[1] - m1, j1 = s.f[1] ? 1 : s.lo[1], k1 = s.f[2] ? 1 : s.lo[2];
+    if (t < s.c[2]) {
+      const int64_t a = (int64_t)s.T[0] * s.T[1], side = t / a, v = t - side * a;
+      k = side ? s.n[2] - 1 : 0;
+      i = (int)(v % s.T[0]) + s.lo[0];
+      j = (int)(v / s.T[0]) + s.lo[1];
+    } else if ((t -= s.c[2]) < s.c[1]) {
+      const int64_t a = (int64_t)s.T[0] * (s.T[2] - m2), side = t / a, v = t - side * a;
+      j = side ? s.n[1] - 1 : 0;
+      i = (int)(v % s.T[0]) + s.lo[0];
+      k = (int)(v / s.T[0]) + k1;
+    } else if ((t -= s.c[1]) < s.c[0]) {
+      const int64_t a = (int64_t)r1 * (s.T[2] - m2), side = t / a, v = t - side * a;
+      i = side ? s.n[0] - 1 : 0;
+      j = (int)(v % r1) + j1;
+      k = (int)(v / r1) + k1;
+    } else {
+      return;
+    }
+  }
+  const int64_t id = stored_index(B, i, j, k);
+  const bool in1 = j >= 0 && j < s.n[1], in2 = k >= 0 && k < s.n[2];
+  if (s.f[0] && (i < 0 || i >= s.n[0]) && in1) return;   // (folded itself)
+  const bool ex = s.f[0] && in1 && in2 && (i == 0 || i == s.n[0] - 1);
+  const bool shear = B.ax[0].bc_lo == BC_SHEAR;
+  Shift sh{0, 0.0, 0.0};
+  if (ex && shear) sh = make_shift(B, fo.qOmega, *fo.tdev + fo.toff);
+  // deposits of cell (ii, jj, kk), kk active, with its ghosts in z
+  auto dz = [&](const TS* a, int ii, int jj, int kk) -> TS {
+    TS v = a[stored_index(B, ii, jj, kk)];
+    if (s.f[2]) {
+      if (kk == s.n[2] - 1) v += a[stored_index(B, ii, jj, -1)];
+      if (kk == 0) v += a[stored_index(B, ii, jj, s.n[2])];
+    }
+    return v;
+  };
+  // and, jj active, with its ghosts in y
+  auto dyz = [&](const TS* a, int ii, int jj, int kk) -> TS {
+    TS v = dz(a, ii, jj, kk);
+    if (s.f[1]) {
+      if (jj == s.n[1] - 1) v += dz(a, ii, -1, kk);
+      if (jj == 0) v += dz(a, ii, s.n[1], kk);
+    }
+    return v;
+  };
+  auto folded = [&](int ch) -> TS {
+    const TS* a = fl.dep[ch];
+    TS v = in1 && in2 ? dyz(a, i, j, k) : in2 ? dz(a, i, j, k) : a[id];
+    if (!ex) return v;
+    if (!shear) {
+      if (i == s.n[0] - 1) v += dyz(a, -1, j, k);
+      if (i == 0) v += dyz(a, s.n[0], j, k);
+      return v;
+    }
+    const int n1 = s.n[1];
+    const bool is_energy = fo.boost_energy && ch == nc;
+    const TS* dy = fl.dep[B.ndim > 1 ? 1 : 0];
+    auto row = [&](int side, int jr) {   // ghost row, energy frame-shifted
+      jr = ((jr % n1) + n1) % n1;
+      const int ig = side ? s.n[0] : -1;
+      double g = double(dyz(a, ig, jr, k));
+      if (is_energy) {
+        const double du = sh.u * double(dyz(dy, ig, jr, k));
+        g = side ? g + du : g - du;
+      }
+      return g;
+    };
+    if (i == 0) {
+      // right ghost row j lands on floor(j + s) (1 - sf) and floor(j + s) + 1 (sf)
+      double add0 = (1.0 - sh.sf) * row(1, j - sh.si);
+      if (sh.sf > 0) add0 += sh.sf * row(1, j - sh.si - 1);
+      v += TS(add0);
+    }
+    if (i == s.n[0] - 1) {
+      // left ghost row j lands on floor(j - s) and floor(j - s) + 1
+      double addn;
+      if (sh.sf > 0) {
+        const int c = sh.si + 1;  // ceil(s)
+        addn = sh.sf * row(0, j + c) + (1.0 - sh.sf) * row(0, j + c - 1);
+      } else {
+        addn = row(0, j + sh.si);
+      }
+      v += TS(addn);
+    }
+    return v;
+  };
+  double D[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if (c > nc) break;
+    const TS v = folded(c);
+    fl.dep[c][id] = v;   // (read by this thread only)
+    D[c] = double(v);
+  }
+  if (FEED && i >= 0 && i < s.n[0] && in1 && in2) feedback(B, fl, nc, i, j, id, D);
+}
+
+// Step start time.
+__global__ void k_set_time(double* t, double v) { t[0] = v; }
+
+void launch_set_time(double* tdev, double v, hipStream_t st) {
+  hipLaunchKernelGGL(k_set_time, dim3(1), dim3(1), 0, st, tdev, v);
+}
+
+template <typename TS> __global__ void k_fill_value(TS* a, int64_t n, TS v) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = v;
 }
 
 // FP64 sums of dV D over every stored cell of the boxes: a grid-stride loop
@@ -1048,8 +1166,8 @@ __global__ void __launch_bounds__(256) k_grid_sums(const Box* boxes, BoxGrid bg,
   }
 }
 
-__global__ void __launch_bounds__(256)
-    k_reduce_grid_partials(const double* __restrict__ part, int n, int nc, DiagDev* dg) {
+// part[0 .. n) added to dg by one workgroup, in a fixed order.
+__device__ void reduce_grid_partials(const double* __restrict__ part, int n, int nc, DiagDev* dg) {
   __shared__ double red[256][4];
   double acc[4] = {0, 0, 0, 0};
 #pragma unroll 4
@@ -1066,6 +1184,35 @@ __global__ void __launch_bounds__(256)
     for (int c = 0; c < nc; ++c) dg->p_grid[c] += red[0][c];
     dg->e_grid += red[0][nc];
   }
+}
+
+__global__ void __launch_bounds__(256)
+    k_reduce_grid_partials(const double* __restrict__ part, int n, int nc, DiagDev* dg) {
+  reduce_grid_partials(part, n, nc, dg);
+}
+
+// After the fold, in one launch: the folded ghost deposits cleared and, in a
+// workgroup past the boxes' (with end), what a step ends with: its grid sums
+// added to the diagnostics, its time advanced, its step counted.
+template <typename TS>
+__global__ void __launch_bounds__(256) k_finish(const Box* boxes, BoxGrid bg, Arr4<TS> dep, int nch, StepEnd end) {
+  if (blockIdx.x >= bg.blk0[bg.n]) {
+    if (end.nparts > 0) reduce_grid_partials(end.part, end.nparts, nch - 1, end.dg);
+    if (threadIdx.x == 0) {
+      *end.tdev += end.dt;
+      if (end.dg) end.dg->steps += 1;
+    }
+    return;
+  }
+  const int e = grid_entry(bg);
+  const Box& B = boxes[bg.box[e]];
+  const GhostSet s = ghost_set(B);
+  const int64_t t = grid_thread(bg, e);
+  if (t >= s.cx + s.cy + s.cz) return;
+  int i, j, k;
+  ghost_cell(s, t, i, j, k);
+  const int64_t id = stored_index(B, i, j, k);
+  for (int c = 0; c < nch; ++c) dep.a[c][id] = TS(0);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1209,89 +1356,89 @@ static inline int box_nc(const Box& B) { return B.geom == GEOM_CART ? B.ndim : 3
 static inline int64_t box_n(const Box& B, int d) { return d < B.ndim ? B.ax[d].n : 1; }
 
 template <typename TS>
-void launch_fill(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
-                 const FView<TS>& fl, double* xg, hipStream_t st) {
+void launch_prepare(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
+                    const FView<TS>& fl, bool fill, double* xg, int nch, int64_t n_stored, hipStream_t st) {
   if (nbox <= 0) return;
   const int nc = box_nc(hb[0]);
-  const Arr4<TS> arrs{{fl.rho, fl.vel[0], fl.vel[1], fl.vel[2]}};
-  const Arr4<TS> vel{{fl.vel[0], fl.vel[1], fl.vel[2], nullptr}};
-  const unsigned na = (unsigned)(nc + 1);
-  const double qOmega = f.q * f.Omega;
+  Prepare<TS> pr{};
+  pr.gas = {{fl.rho, fl.vel[0], fl.vel[1], fl.vel[2]}};
+  pr.na = fill ? nc + 1 : 0;
+  pr.xg = xg;
+  pr.qOmega = f.q * f.Omega;
+  pr.toff = toff;
+  pr.tdev = tdev;
   // the v_y ghosts across a shear face carry the boost -/+ q Omega L_x,
   // except for the residual velocities of orbital advection
-  const int boost = f.kind == FORCE_SHEARBOX;
-  if (xg)
-    for_box_grids(hb, nbox, [](const Box& B) { return B.xg_base >= 0; },
-                  [](const Box& B) { return blocks_for((box_n(B, 1) + 2) * (box_n(B, 2) + 2)); },
-                  [&](const BoxGrid& g, uint32_t nb) {
-                    hipLaunchKernelGGL((k_fill_xghost<TS>), dim3(nb, (unsigned)nc), dim3(256), 0, st, boxes_d, g,
-                                       vel, xg, qOmega, tdev, toff, boost);
-                  });
-  for_box_grids(hb, nbox, [](const Box& B) { return B.ax[0].bc_lo != BC_OPEN; },
-                [](const Box& B) { return blocks_for(box_n(B, 1) * box_n(B, 2)); },
-                [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_fill_x<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, arrs, boost,
-                                     qOmega, tdev, toff);
-                });
-  for_box_grids(hb, nbox, [](const Box& B) { return B.ax[1].bc_lo == BC_PERIODIC; },
-                [](const Box& B) { return blocks_for((box_n(B, 0) + 2) * box_n(B, 2)); },
-                [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_fill_y<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, arrs);
-                });
-  for_box_grids(hb, nbox, [](const Box& B) { return B.ndim > 2 && B.ax[2].bc_lo == BC_PERIODIC; },
-                [](const Box& B) { return blocks_for((box_n(B, 0) + 2) * (box_n(B, 1) + 2)); },
-                [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_fill_z<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, arrs);
-                });
+  pr.boost = f.kind == FORCE_SHEARBOX;
+  pr.dep = {{fl.dep[0], fl.dep[1], fl.dep[2], fl.dep[3]}};
+  pr.n = n_stored;
+  bool clear = nch > 0 && n_stored > 0;   // with the first launch
+  auto run = [&](const BoxGrid& g, uint32_t nb) {
+    pr.nch = clear ? nch : 0;
+    if (clear) nb += (uint32_t)nch * blocks256((n_stored + CLEAR_PER - 1) / CLEAR_PER);
+    clear = false;
+    hipLaunchKernelGGL((k_prepare<TS>), dim3(nb), dim3(256), 0, st, boxes_d, g, pr);
+  };
+  if (fill)
+    for_box_grids(hb, nbox, [](const Box&) { return true; },
+                  [&](const Box& B) {
+                    return (uint32_t)(nc + 1) * blocks256(fill_cells(B)) +
+                           (xg ? (uint32_t)nc * blocks256(xghost_cells(B)) : 0u);
+                  },
+                  run);
+  if (clear) run(BoxGrid{}, 0);
 }
 
 template <typename TS>
 void launch_fold(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
-                 const FView<TS>& fl, hipStream_t st) {
+                 const FView<TS>& fl, bool feedback, hipStream_t st) {
   if (nbox <= 0) return;
-  const int nc = box_nc(hb[0]);
-  const double qOmega = f.q * f.Omega;
+  // the energy term of the boost: standard shearing box only
+  const Fold<TS> fo{f.q * f.Omega, toff, tdev, f.kind == FORCE_SHEARBOX};
+  for_box_grids(hb, nbox, [](const Box&) { return true; },
+                [&](const Box& B) {
+                  const FoldSet s = fold_set(B);
+                  return blocks256(s.c[0] + s.c[1] + s.c[2]) + (feedback ? blocks256(B.ncell) : 0u);
+                },
+                [&](const BoxGrid& g, uint32_t nb) {
+                  if (feedback)
+                    hipLaunchKernelGGL((k_fold<TS, true, true>), dim3(nb), dim3(256), 0, st, boxes_d, g, fl, fo);
+                  else
+                    hipLaunchKernelGGL((k_fold<TS, true, false>), dim3(nb), dim3(256), 0, st, boxes_d, g, fl, fo);
+                });
+}
+
+template <typename TS>
+void launch_finish(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, const StepEnd* end,
+                   hipStream_t st) {
+  if (nbox <= 0) return;
+  const int nch = box_nc(hb[0]) + 1;
   const Arr4<TS> deps{{fl.dep[0], fl.dep[1], fl.dep[2], fl.dep[3]}};
-  const unsigned na = (unsigned)(nc + 1);
-  for_box_grids(hb, nbox, [](const Box& B) { return B.ndim > 2 && B.ax[2].bc_lo == BC_PERIODIC; },
-                [](const Box& B) { return blocks_for((box_n(B, 0) + 2) * (box_n(B, 1) + 2)); },
-                [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_fold_z<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, deps);
-                });
-  for_box_grids(hb, nbox, [](const Box& B) { return B.ax[1].bc_lo == BC_PERIODIC; },
-                [](const Box& B) { return blocks_for((box_n(B, 0) + 2) * box_n(B, 2)); },
-                [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_fold_y<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, deps);
-                });
-  // the energy channel reads the D_y ghosts, which no thread of this launch
-  // writes (they are cleared by the next one); the energy term of the boost:
-  // standard shearing box only
-  const TS* dy = fl.dep[hb[0].ndim > 1 ? 1 : 0];
-  const int boost_energy = f.kind == FORCE_SHEARBOX;
-  auto xfold = [](const Box& B) { return B.ax[0].bc_lo != BC_OPEN; };
-  auto xblocks = [](const Box& B) { return blocks_for(box_n(B, 1) * box_n(B, 2)); };
-  for_box_grids(hb, nbox, xfold, xblocks, [&](const BoxGrid& g, uint32_t nb) {
-    hipLaunchKernelGGL((k_fold_x<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, deps, dy, boost_energy,
-                       qOmega, tdev, toff);
-  });
-  for_box_grids(hb, nbox, xfold, xblocks, [&](const BoxGrid& g, uint32_t nb) {
-    hipLaunchKernelGGL((k_clear_x_ghosts<TS>), dim3(nb, na), dim3(256), 0, st, boxes_d, g, deps);
-  });
+  bool pend = end != nullptr;   // with the first launch (nothing in the others reads what it writes)
+  auto run = [&](const BoxGrid& g, uint32_t nb) {
+    hipLaunchKernelGGL((k_finish<TS>), dim3(nb + (pend ? 1 : 0)), dim3(256), 0, st, boxes_d, g, deps, nch,
+                       end ? *end : StepEnd{});
+    pend = false;
+  };
+  for_box_grids(hb, nbox, [](const Box&) { return true; }, [](const Box& B) { return blocks256(fill_cells(B)); }, run);
+  if (pend) run(BoxGrid{}, 0);
 }
 
 template <typename TS>
 void launch_feedback(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, hipStream_t st) {
-  for_box_grids(hb, nbox, [](const Box&) { return true; }, [](const Box& B) { return blocks_for(B.ncell); },
+  for_box_grids(hb, nbox, [](const Box&) { return true; }, [](const Box& B) { return blocks256(B.ncell); },
                 [&](const BoxGrid& g, uint32_t nb) {
-                  hipLaunchKernelGGL((k_feedback<TS>), dim3(nb), dim3(256), 0, st, boxes_d, g, fl);
+                  hipLaunchKernelGGL((k_fold<TS, false, true>), dim3(nb), dim3(256), 0, st, boxes_d, g, fl,
+                                     Fold<TS>{});
                 });
 }
 
 template <typename TS>
-void launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, DiagDev* dg, double* part,
-                      hipStream_t st) {
-  if (nbox <= 0) return;
+int launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, DiagDev* dg, double* part,
+                     hipStream_t st) {
+  if (nbox <= 0) return 0;
   const int nc = box_nc(hb[0]);
+  int pend = 0;
   // blocks shared out in proportion to the stored cells of each launch's
   // boxes (at most GRID_SUM_BLOCKS + MB_BOXES in all)
   for (int b0 = 0; b0 < nbox; b0 += MB_BOXES) {
@@ -1302,22 +1449,18 @@ void launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<T
     for_box_grids(hb + b0, b1 - b0, [](const Box& B) { return B.nstore > 0; },
                   [&](const Box& B) {
                     const int64_t share = (int64_t)GRID_SUM_BLOCKS * B.nstore / tot;
-                    return (uint32_t)std::max<int64_t>(1, std::min<int64_t>(blocks_for(B.nstore), share));
+                    return (uint32_t)std::max<int64_t>(1, std::min<int64_t>(blocks256(B.nstore), share));
                   },
                   [&](BoxGrid g, uint32_t nb) {
                     for (int e = 0; e < g.n; ++e) g.box[e] += b0;
+                    if (pend)   // (the slots are free again after this)
+                      hipLaunchKernelGGL(k_reduce_grid_partials, dim3(1), dim3(256), 0, st, (const double*)part, pend,
+                                         nc, dg);
                     hipLaunchKernelGGL((k_grid_sums<TS>), dim3(nb), dim3(256), 0, st, boxes_d, g, fl, part);
-                    hipLaunchKernelGGL(k_reduce_grid_partials, dim3(1), dim3(256), 0, st, (const double*)part,
-                                       (int)nb, nc, dg);
+                    pend = (int)nb;
                   });
   }
-}
-
-template <typename TS> void launch_clear_deposits(const FView<TS>& fl, int nch, int64_t n, hipStream_t st) {
-  if (n <= 0 || nch <= 0) return;
-  const Arr4<TS> deps{{fl.dep[0], fl.dep[1], fl.dep[2], fl.dep[3]}};
-  hipLaunchKernelGGL((k_fill_values<TS>), dim3(blocks_for(n), (unsigned)nch), dim3(256), 0, st, deps, n,
-                     TS(0));
+  return pend;
 }
 
 template <typename TS> void launch_fill_value(TS* a, int64_t n, TS v, hipStream_t st) {
@@ -1361,15 +1504,16 @@ DUST_INST(float, float, float)
 DUST_INST(double, double, double)
 
 #define DUST_INST_GRID(TS)                                                                        \
-  template void launch_fill<TS>(const Box*, int, const Box*, const Forces&, const double*, double,   \
-                                const FView<TS>&, double*, hipStream_t);                          \
+  template void launch_prepare<TS>(const Box*, int, const Box*, const Forces&, const double*, double, \
+                                   const FView<TS>&, bool, double*, int, int64_t, hipStream_t);   \
   template void launch_fold<TS>(const Box*, int, const Box*, const Forces&, const double*, double,   \
-                                const FView<TS>&, hipStream_t);                                   \
+                                const FView<TS>&, bool, hipStream_t);                             \
+  template void launch_finish<TS>(const Box*, int, const Box*, const FView<TS>&, const StepEnd*,  \
+                                  hipStream_t);                                                   \
   template void launch_feedback<TS>(const Box*, int, const Box*, const FView<TS>&, hipStream_t);     \
-  template void launch_grid_sums<TS>(const Box*, int, const Box*, const FView<TS>&, DiagDev*, double*, \
-                                     hipStream_t);                                                \
-  template void launch_fill_value<TS>(TS*, int64_t, TS, hipStream_t);                              \
-  template void launch_clear_deposits<TS>(const FView<TS>&, int, int64_t, hipStream_t);
+  template int launch_grid_sums<TS>(const Box*, int, const Box*, const FView<TS>&, DiagDev*, double*, \
+                                    hipStream_t);                                                 \
+  template void launch_fill_value<TS>(TS*, int64_t, TS, hipStream_t);
 
 DUST_INST_GRID(float)
 DUST_INST_GRID(double)

@@ -79,29 +79,42 @@ void launch_mass_density(const PView<TS>& p, const Box* boxes, int nbox, int geo
 // The per-box grid operations below take the host copies of the boxes (hb,
 // nbox; geometry and ndim shared) and their device table, and launch each
 // kernel once for up to 16 boxes.
-// Ghost fill of the gas at *tdev + toff; with xg (the context's FP64 x-ghost
-// buffer), also the FP64 x-ghost layers of shear-periodic boxes.
+// Before a step: with fill, the gas ghosts at *tdev + toff and, with xg (the
+// context's FP64 x-ghost buffer), the FP64 x-ghost layers of shear-periodic
+// boxes; the first nch deposit channels cleared over n_stored cells.
 template <typename TS>
-void launch_fill(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
-                 const FView<TS>& fl, double* xg, hipStream_t st);
+void launch_prepare(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
+                    const FView<TS>& fl, bool fill, double* xg, int nch, int64_t n_stored, hipStream_t st);
+// Ghost deposits added to the cells they are images of (launch_finish clears
+// them), with feedback then the momentum deposits to the gas.
 template <typename TS>
 void launch_fold(const Box* hb, int nbox, const Box* boxes_d, const Forces& f, const double* tdev, double toff,
-                 const FView<TS>& fl, hipStream_t st);
+                 const FView<TS>& fl, bool feedback, hipStream_t st);
+// What a step ends with: the partials of its grid sums (nparts; 0: none) to
+// dg, its time advanced by dt, its step counted in dg (or null).
+struct StepEnd {
+  const double* part;
+  int nparts;
+  DiagDev* dg;
+  double* tdev;
+  double dt;
+};
+// Folded ghost deposits cleared; with end, the end of a step.
+template <typename TS>
+void launch_finish(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, const StepEnd* end,
+                   hipStream_t st);
 void launch_set_time(double* tdev, double v, hipStream_t st);
-// advance the step time by dt; count: the diagnostics whose step count goes up (or null)
-void launch_advance_time(double* tdev, double dt, DiagDev* count, hipStream_t st);
 template <typename TS>
 void launch_feedback(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, hipStream_t st);
-// FP64 grid sums of the boxes, added to dg; part: GRID_SUM_PARTS * 4
-// doubles of scratch.
+// FP64 grid sums of the boxes; part: GRID_SUM_PARTS * 4 doubles of scratch.
+// Returns the number of partials in it that launch_finish is to add to dg
+// (those of earlier launches of many boxes are added on the way).
 static constexpr int GRID_SUM_BLOCKS = 2048;
 static constexpr int GRID_SUM_PARTS = GRID_SUM_BLOCKS + 16;
 template <typename TS>
-void launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, DiagDev* dg, double* part,
-                      hipStream_t st);
+int launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, DiagDev* dg, double* part,
+                     hipStream_t st);
 template <typename TS> void launch_fill_value(TS* a, int64_t n, TS v, hipStream_t st);
-// Zero the first nch deposit channels over n stored cells (one launch).
-template <typename TS> void launch_clear_deposits(const FView<TS>& fl, int nch, int64_t n, hipStream_t st);
 
 // Binning (dust_bin.hip).  Workspace sizes in bytes for n particles.
 struct BinWork {
