@@ -27,6 +27,9 @@ static constexpr int BIN_MAX_BITS = 9;
 // below this many keys, blocks of 1024 instead of 4096 (4096 would leave CUs idle)
 static constexpr int64_t BIN_FEW = 1 << 19;
 
+// up to this many blocks, a pass without a scan
+static constexpr int64_t BIN_DIRECT = 256;
+
 // Sort keys from the cells, KEYS_PER particles of a thread (their loads
 // issue together).
 static constexpr int KEYS_PER = 4;
@@ -67,9 +70,9 @@ __device__ __forceinline__ uint32_t bin_block(uint32_t nblocks) {
 }
 
 // Digit histogram of every block of BIN_THREADS * ITEMS keys: hist[digit *
-// nblocks + block].  Only the first lane of a run of equal digits adds (keys
+// nblocks + block], with DIRECT hist[block * NDIG + digit].  Only the first lane of a run of equal digits adds (keys
 // that are nearly sorted would queue on one counter).
-template <int NDIG, int ITEMS>
+template <int NDIG, int ITEMS, bool DIRECT>
 __global__ void __launch_bounds__(BIN_THREADS)
     k_digit_hist(const uint32_t* __restrict__ key, uint32_t n, int shift, int nbits, uint32_t* __restrict__ hist,
                  uint32_t nblocks) {
@@ -77,7 +80,7 @@ __global__ void __launch_bounds__(BIN_THREADS)
   const int t = threadIdx.x, lane = t & 63;
   const uint32_t ndig = 1u << nbits, mask = ndig - 1;
   const uint32_t b = bin_block(nblocks);
-  for (uint32_t d = t; d < ndig; d += BIN_THREADS) h[d] = 0;
+  for (uint32_t d = t; d < (DIRECT ? NDIG : ndig); d += BIN_THREADS) h[d] = 0;
   __syncthreads();
   const uint32_t base = b * (uint32_t)(BIN_THREADS * ITEMS);
   uint32_t k[ITEMS];
@@ -101,16 +104,21 @@ __global__ void __launch_bounds__(BIN_THREADS)
     }
   }
   __syncthreads();
-  for (uint32_t d = t; d < ndig; d += BIN_THREADS) hist[(size_t)d * nblocks + b] = h[d];
+  if constexpr (DIRECT) {
+    for (uint32_t d = t; d < NDIG; d += BIN_THREADS) hist[(size_t)b * NDIG + d] = h[d];
+  } else {
+    for (uint32_t d = t; d < ndig; d += BIN_THREADS) hist[(size_t)d * nblocks + b] = h[d];
+  }
 }
 
 // One radix pass of one block: every wave ranks its 64 * ITEMS consecutive
 // keys among its own (round by round of 64, ballots for lanes with equal
 // digits, counters of its own for the rounds), the counters of the waves
 // become places in stable digit order, the keys and then the values are put
-// there in LDS and written out run by run.  offs: the scanned histogram.
+// there in LDS and written out run by run.  offs: the scanned histogram; with
+// DIRECT the histogram itself, which every block sums for its own places.
 // val_in = nullptr: values are the element indices (first pass).
-template <int NDIG, int ITEMS>
+template <int NDIG, int ITEMS, bool DIRECT>
 __global__ void __launch_bounds__(BIN_THREADS)
     k_digit_scatter(const uint32_t* __restrict__ key_in, const uint32_t* __restrict__ val_in, uint32_t n, int shift,
                     int nbits, const uint32_t* __restrict__ offs, uint32_t nblocks, uint32_t* __restrict__ key_out,
@@ -122,6 +130,7 @@ __global__ void __launch_bounds__(BIN_THREADS)
   __shared__ uint32_t goff[NDIG];
   __shared__ uint16_t cnt[BIN_WAVES][NDIG];
   __shared__ uint32_t wsum[BIN_WAVES];
+  __shared__ __align__(16) uint32_t part[2][DIRECT ? BIN_WAVES : 1][DIRECT ? NDIG : 4];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const uint32_t ndig = 1u << nbits, mask = ndig - 1;
   const uint32_t b = bin_block(nblocks), base = b * (uint32_t)KEYS;
@@ -140,6 +149,66 @@ __global__ void __launch_bounds__(BIN_THREADS)
     v[c] = l < nloc ? (val_in ? val_in[base + l] : base + l) : 0u;
   }
   for (int d = t; d < BIN_WAVES * NDIG; d += BIN_THREADS) (&cnt[0][0])[d] = 0;
+  // DIRECT: keys of this thread's digits in the blocks before this one (gpre)
+  // and in all; then, with the keys of lower digits, the first place of each
+  uint32_t gpre[P];
+  if constexpr (DIRECT) {
+    // a wave takes every fourth block, a lane four digits of it, U blocks
+    // whose loads issue together (one block after another, a thread per
+    // digit, was slower from some 100 blocks on than the scan)
+    constexpr int Q = NDIG / 256, U = 16 / Q;
+    const uint4* rows = reinterpret_cast<const uint4*>(offs) + lane;
+    uint4 all4[Q] = {}, bef4[Q] = {};
+    for (uint32_t q = wv; q < nblocks; q += BIN_WAVES * U) {
+      uint4 x[U][Q];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < Q; ++j)
+          x[u][j] = q + BIN_WAVES * u < nblocks ? rows[(size_t)(q + BIN_WAVES * u) * (NDIG / 4) + 64 * j]
+                                                : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+          const bool lower = q + BIN_WAVES * u < b;
+          const uint4 y = x[u][j];
+          all4[j].x += y.x, all4[j].y += y.y, all4[j].z += y.z, all4[j].w += y.w;
+          bef4[j].x += lower ? y.x : 0u, bef4[j].y += lower ? y.y : 0u;
+          bef4[j].z += lower ? y.z : 0u, bef4[j].w += lower ? y.w : 0u;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      reinterpret_cast<uint4*>(part[0][wv])[64 * j + lane] = all4[j];
+      reinterpret_cast<uint4*>(part[1][wv])[64 * j + lane] = bef4[j];
+    }
+    __syncthreads();
+    uint32_t before[P] = {}, all[P] = {}, sum = 0;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+      for (int w = 0; w < BIN_WAVES; ++w) {
+        all[j] += part[0][w][t * P + j];
+        before[j] += part[1][w][t * P + j];
+      }
+#pragma unroll
+    for (int j = 0; j < P; ++j) sum += all[j];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    uint32_t low = incl - sum;
+    for (int w = 0; w < wv; ++w) low += wsum[w];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      gpre[j] = before[j] + low;
+      low += all[j];
+    }
+  }
   __syncthreads();
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
@@ -183,7 +252,8 @@ __global__ void __launch_bounds__(BIN_THREADS)
   for (int j = 0; j < P; ++j) {
     const uint32_t d = (uint32_t)(t * P + j);
     // a place p of digit d goes to goff[d] + p
-    goff[d] = (d < ndig ? offs[(size_t)d * nblocks + b] : 0u) - start;
+    if constexpr (DIRECT) goff[d] = gpre[j] - start;
+    else goff[d] = (d < ndig ? offs[(size_t)d * nblocks + b] : 0u) - start;
     uint32_t q = start;
 #pragma unroll
     for (int w = 0; w < BIN_WAVES; ++w) {
@@ -260,9 +330,12 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // A sort's passes: ITEMS keys of a thread (few where the launch would not
 // fill the chip), and as few passes as the histogram's room allows.
+// direct: no scan (three launches); every block of the scatter sums the
+// histogram's columns, which are then block by block.
 struct BinPlan {
   int items, npass, nbits;   // nbits: of every pass but the last, which has the rest
   int64_t nblocks;
+  bool direct;
 };
 static BinPlan bin_plan(int64_t n, int64_t nbins, size_t hist_words) {
   int bits = 1;
@@ -273,6 +346,8 @@ static BinPlan bin_plan(int64_t n, int64_t nbins, size_t hist_words) {
   for (;;) {
     p.nbits = (bits + p.npass - 1) / p.npass;
     p.nblocks = ceil_div(n, BIN_THREADS * p.items);
+    p.direct = p.items == 4 && p.nblocks <= BIN_DIRECT &&
+               (size_t)p.nblocks * (p.nbits <= 8 ? 256 : 512) <= hist_words;
     if (((size_t)p.nblocks << p.nbits) <= hist_words) return p;
     if (p.items == 4) p.items = 16;   // larger blocks, then digits of 8 bits: these always fit
     else ++p.npass;
@@ -352,17 +427,16 @@ int launch_bin(const int32_t* cell, int64_t n, const Box* boxes_dev, int nbox, i
     auto pass = [&](auto hist_kern, auto scatter_kern) {
       hipLaunchKernelGGL(hist_kern, grid, block, 0, st, (const uint32_t*)w.key[cur], (uint32_t)n, shift, nb, w.hist,
                          (uint32_t)plan.nblocks);
-      scan_exclusive(w.hist, (int64_t)plan.nblocks << nb, w.scan_tmp, st);
+      if (!plan.direct) scan_exclusive(w.hist, (int64_t)plan.nblocks << nb, w.scan_tmp, st);
       hipLaunchKernelGGL(scatter_kern, grid, block, 0, st, (const uint32_t*)w.key[cur], vin, (uint32_t)n, shift, nb,
                          (const uint32_t*)w.hist, (uint32_t)plan.nblocks, w.key[1 - cur], w.val[1 - cur]);
     };
-    if (plan.nbits <= 8) {
-      if (plan.items == 4) pass(k_digit_hist<256, 4>, k_digit_scatter<256, 4>);
-      else pass(k_digit_hist<256, 16>, k_digit_scatter<256, 16>);
-    } else {
-      if (plan.items == 4) pass(k_digit_hist<512, 4>, k_digit_scatter<512, 4>);
-      else pass(k_digit_hist<512, 16>, k_digit_scatter<512, 16>);
-    }
+    if (plan.direct && plan.nbits <= 8) pass(k_digit_hist<256, 4, true>, k_digit_scatter<256, 4, true>);
+    else if (plan.direct) pass(k_digit_hist<512, 4, true>, k_digit_scatter<512, 4, true>);
+    else if (plan.nbits <= 8 && plan.items == 4) pass(k_digit_hist<256, 4, false>, k_digit_scatter<256, 4, false>);
+    else if (plan.nbits <= 8) pass(k_digit_hist<256, 16, false>, k_digit_scatter<256, 16, false>);
+    else if (plan.items == 4) pass(k_digit_hist<512, 4, false>, k_digit_scatter<512, 4, false>);
+    else pass(k_digit_hist<512, 16, false>, k_digit_scatter<512, 16, false>);
     cur = 1 - cur;
   }
   if (perm_out)
