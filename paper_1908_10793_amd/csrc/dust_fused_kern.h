@@ -703,6 +703,12 @@ __global__ void __launch_bounds__(FUSED_THREADS)
 // ghosts).  Their diagnostic sums go to partial slots part0 .. part0 +
 // DEFER_BLOCKS - 1; slot word 6 counts them.  Removals through open faces
 // and the sticky flags go to dg directly, as in the tile kernel.
+//
+// Usually they are few, and the kernel is as long as one particle's chain of
+// loads: they are dealt to all waves before the lanes of one, and what a
+// particle reads is loaded in few batches (32^3 shearing box, those that cross
+// the x faces in the first half drift: 21 us; 44 with waves filled one after
+// the other, the x-ghost values and the cell volumes read cell by cell).
 template <typename TS, typename A, int GEOM, int NDIM, bool U>
 __global__ void __launch_bounds__(256)
     k_fused_deferred(PView<TS> p, ShadowView<TS> sh, const uint32_t* __restrict__ src_index,
@@ -717,7 +723,10 @@ __global__ void __launch_bounds__(256)
   const double t0 = *tdev;
   const A h = A(0.5) * dt;
   double s_j[3] = {0, 0, 0}, s_e = 0, s_abs = 0, s_cells = 0, s_n = 0;
-  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
+  const uint32_t waves = gridDim.x * (blockDim.x / 64), ln = threadIdx.x & 63;
+  const uint32_t per = n < waves * 64 ? (n + waves - 1) / waves : 64;
+  for (uint32_t e = (blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * per + ln; ln < per && e < n;
+       e += waves * per) {
     // slot; after a rebinning its packed particle is written there first,
     // which then holds what the step does not change
     const int64_t i = list[e];
@@ -754,9 +763,21 @@ __global__ void __launch_bounds__(256)
       A v[3] = {A(0), A(0), A(0)};
       double vaz = 0.0;   // azimuthal component in FP64 (AZ)
       // The stencil's field values are loaded unconditionally, so that the
-      // loads issue together; x ghosts of a shear-periodic box then take the
-      // FP64 ghost layer's value (a rare branch).
-      const bool xghost = xg && B.xg_base >= 0 && (idx[0] <= 0 || idx[0] >= B.ax[0].n - 1);
+      // loads issue together; x ghosts of a shear-periodic box take the FP64
+      // ghost layer's values, loaded before (most deferred particles of such a
+      // box are next to its x faces).
+      const bool layer = GEOM == GEOM_CART && NDIM == 3 && xg && B.xg_base >= 0;
+      const bool glo = layer && idx[0] <= 0, ghi = layer && idx[0] >= B.ax[0].n - 1;
+      double gx[2 * c2 + 1][3][3];
+      if (glo != ghi) {
+#pragma unroll
+        for (int c = -c2; c <= c2; ++c)
+#pragma unroll
+          for (int bb = -1; bb <= 1; ++bb)
+#pragma unroll
+            for (int m = 0; m < nc; ++m)
+              gx[c + c2][bb + 1][m] = gas_comp(B, fl, xg, m, glo ? -1 : B.ax[0].n, idx[1] + bb, idx[2] + c);
+      }
 #pragma unroll
       for (int c = -c2; c <= c2; ++c)
 #pragma unroll
@@ -768,12 +789,18 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
             for (int m = 0; m < nc; ++m) g[a + 1][m] = double(fl.vel[m][id]);
           }
-          if (xghost) {
+          if (glo && ghi) {   // (one cell along x)
 #pragma unroll
-            for (int a = -1; a <= 1; ++a)
+            for (int a = -1; a <= 1; a += 2)
 #pragma unroll
               for (int m = 0; m < nc; ++m)
                 g[a + 1][m] = gas_comp(B, fl, xg, m, idx[0] + a, idx[1] + bb, idx[2] + c);
+          } else if (glo || ghi) {
+#pragma unroll
+            for (int m = 0; m < nc; ++m) {
+              g[0][m] = glo ? gx[c + c2][bb + 1][m] : g[0][m];
+              g[2][m] = glo ? g[2][m] : gx[c + c2][bb + 1][m];
+            }
           }
 #pragma unroll
           for (int a = -1; a <= 1; ++a) {
@@ -817,15 +844,23 @@ __global__ void __launch_bounds__(256)
       }
       q[nc] = -m * o.e;
       if (sums) s_e -= double(q[nc]);
+      // (whatever the adds need of the box is read before the first of them:
+      // the compiler moves no load over an atomic)
+      double iv[3][3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int a = -1; a <= 1; ++a) iv[d][a + 1] = d < NDIM ? B.ax[d].ivol[idx[d] + a + 1] : 1.0;
+      const int64_t id0 = stored_index(B, idx[0], idx[1], idx[2]), gy = B.g0, gz = gy * B.g1;
 #pragma unroll
       for (int cc = -c2; cc <= c2; ++cc)
 #pragma unroll
         for (int bb = -1; bb <= 1; ++bb)
 #pragma unroll
           for (int a = -1; a <= 1; ++a) {
-            const int ii = idx[0] + a, jj = idx[1] + bb, kk = idx[2] + cc;
-            const A w = s.w[0][a + 1] * s.w[1][bb + 1] * s.w[2][cc + 1] * A(inv_volume(B, ii, jj, kk));
-            const int64_t id = stored_index(B, ii, jj, kk);
+            const double v = c2 ? iv[0][a + 1] * iv[1][bb + 1] * iv[2][cc + 1] : iv[0][a + 1] * iv[1][bb + 1];
+            const A w = s.w[0][a + 1] * s.w[1][bb + 1] * s.w[2][cc + 1] * A(v);
+            const int64_t id = id0 + a + gy * bb + gz * cc;
 #pragma unroll
             for (int k = 0; k <= nc; ++k) unsafeAtomicAdd(&fl.dep[k][id], TS(w * q[k]));
           }
