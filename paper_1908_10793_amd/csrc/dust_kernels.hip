@@ -1104,11 +1104,12 @@ __global__ void __launch_bounds__(256) k_fold(const Box* boxes, BoxGrid bg, FVie
   double D[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    if (c > nc) break;
-    const TS v = folded(c);
-    fl.dep[c][id] = v;   // (read by this thread only)
-    D[c] = double(v);
+    if (c <= nc) D[c] = double(folded(c));
   }
+  // (stores last: the channels' loads issue together)
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c <= nc) fl.dep[c][id] = TS(D[c]);
   if (FEED && i >= 0 && i < s.n[0] && in1 && in2) feedback(B, fl, nc, i, j, id, D);
 }
 
