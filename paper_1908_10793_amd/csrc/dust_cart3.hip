@@ -22,13 +22,15 @@ DUST_C3_AUX_SHAPES(extern)
 // (descending, ties by tile-local index) within each bank group, and ordered
 // by (rank, group): a wave of a full tile takes 4 ranks of every group, and
 // every 16 consecutive lanes hold one cell of each group.  (rx, ry: x and y
-// extents of the tile kernel's gas window.)
+// extents of the tile kernel's gas window.)  A cell looks for its rank among
+// its group only: 32^3 box of 131 k particles 12 us (against all cells of the
+// tile 32), 128^3 box of 16.8 M 128 us (175), where the writes of the pairs
+// bound it.
 __global__ void __launch_bounds__(256)
     k_c3_level_perm(const TileDesc* __restrict__ tiles, const uint32_t* __restrict__ perm,
                     const int64_t* __restrict__ bin_start, uint8_t* __restrict__ tmap,
                     uint32_t* __restrict__ lm, uint32_t* __restrict__ order_slot, int rx, int ry) {
-  __shared__ int cnt_s[256];
-  __shared__ int grp_s[256];
+  __shared__ uint64_t list[256];   // the cells group by group
   __shared__ int gsize[16];
   __shared__ uint8_t map_s[256];
   const TileDesc td = tiles[blockIdx.x];
@@ -40,18 +42,21 @@ __global__ void __launch_bounds__(256)
     const int lx = t % td.ex, ly = (t / td.ex) % td.ey, lz = t / (td.ex * td.ey);
     g = ((lx + FUSED_HALO) + rx * ((ly + FUSED_HALO) + ry * (lz + FUSED_HALO))) & 15;
   }
-  cnt_s[t] = c;
-  grp_s[t] = g;
   if (t < 16) gsize[t] = 0;
   __syncthreads();
-  if (t < nct) atomicAdd(&gsize[g], 1);
+  int at = 0;
+  if (t < nct) at = atomicAdd(&gsize[g], 1);
+  __syncthreads();
+  // a cell is compared with those of its group only (their places in the list
+  // are in no order, their keys are)
+  const uint64_t key = ((uint64_t)(uint32_t)c << 8) | (uint32_t)(255 - t);
+  int g0 = 0;
+  for (int k = 0; k < 16; ++k) g0 += k < g ? gsize[k] : 0;
+  if (t < nct) list[g0 + at] = key;
   __syncthreads();
   if (t < nct) {
     int rank = 0;
-    for (int u = 0; u < nct; ++u) {
-      const int cu = cnt_s[u];
-      rank += (grp_s[u] == g && (cu > c || (cu == c && u < t))) ? 1 : 0;
-    }
+    for (int u = 0; u < gsize[g]; ++u) rank += list[g0 + u] > key ? 1 : 0;
     // position in (rank, group) order
     int pos = 0;
     for (int k = 0; k < 16; ++k) {
