@@ -155,6 +155,7 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
 #define DUST_C3(TX, TY, TZ)                                                                             \
   launch_c3_shape<TX, TY, TZ>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st)
   const bool cells = mv.sh.rec && mv.order_src;
+  const int nparts = plan.ntiles * (cells ? cells_split(plan.ntiles, p.n) : 1);
   if (cells)
     launch_c3_cells(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st);
   else
@@ -171,8 +172,8 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
   hipLaunchKernelGGL((k_fused_deferred<float, float, GEOM_CART, 3, true>), dim3(DEFER_BLOCKS), dim3(256), 0, st,
                      p, cells ? ShadowView<float>{nullptr, nullptr} : mv.sh, mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
                      (const uint32_t*)plan.defer_list, (const uint32_t*)plan.defer_count, plan.part_d,
-                     plan.ntiles, (int)sums, dg);
-  launch_reduce_fused<float>(plan, dg, sums, p, mv, bin_start, st);
+                     nparts, (int)sums, dg);
+  launch_reduce_fused<float>(plan, nparts, dg, sums, p, mv, bin_start, st);
 }
 
 void launch_c3_aux(const FusedPlan& plan, const PView<float>& p, const Box* boxes_d, int nbox,

@@ -16,7 +16,7 @@ namespace dust {
 
 template <bool SB, bool SMALL>
 __global__ void __launch_bounds__(RUN_THREADS)
-    k_c3_cells(const TileDesc* __restrict__ tiles, int TX, int TY, int TZ, PView<float> p, ShadowView<float> sh,
+    k_c3_cells(const TileDesc* __restrict__ tiles, int split, int TX, int TY, int TZ, PView<float> p, ShadowView<float> sh,
                const Box* __restrict__ boxes, FView<float> fl, Forces f, const Species* __restrict__ sp, float dt,
                const double* __restrict__ tdev, const int64_t* __restrict__ bin_start,
                const double* __restrict__ xg, DiagDev* dg, double* __restrict__ part, int sums,
@@ -33,12 +33,12 @@ __global__ void __launch_bounds__(RUN_THREADS)
   __shared__ float4 sp_k[DUST_MAX_SPECIES];
   __shared__ float2 sp_w[DUST_MAX_SPECIES];
   const int tid = threadIdx.x;
-  const TileDesc td = tiles[blockIdx.x];
+  const TileDesc td = tiles[blockIdx.x / (unsigned)split];
   const Box& B = boxes[td.box];
   const C3Box cb = c3_box(B, dt);
   const int ox = td.i0 - 1, oy = td.j0 - 1, oz = td.k0 - 1;
-  const uint32_t s0 = (uint32_t)bin_start[td.key0],
-                 s1 = (uint32_t)bin_start[td.key0 + (int64_t)td.ex * td.ey * td.ez];
+  uint32_t s0 = (uint32_t)bin_start[td.key0], s1 = (uint32_t)bin_start[td.key0 + (int64_t)td.ex * td.ey * td.ez];
+  if (split > 1) tile_piece(s0, s1, split);
   float s_j0 = 0.0f, s_j1 = 0.0f, s_j2 = 0.0f, s_e = 0.0f, s_abs = 0.0f, s_cells = 0.0f;
   uint32_t flags_acc = 0, n_rem = 0;
   if (s0 < s1) {
@@ -334,7 +334,8 @@ void launch_c3_cells(const FusedPlan& plan, const PView<float>& p, const FusedMo
   const size_t wc = (size_t)(t.t[0] + 2) * (t.t[1] + 2) * (t.t[2] + 2);
   const size_t lds = wc * (4 * sizeof(double) + sizeof(float4)) + (size_t)(t.t[0] + 2) * sizeof(float2);
   auto run = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(RUN_THREADS), lds, st, plan.tiles_d, t.t[0], t.t[1], t.t[2], p,
+    const int split = cells_split(plan.ntiles, p.n);
+    hipLaunchKernelGGL(kern, dim3(plan.ntiles * split), dim3(RUN_THREADS), lds, st, plan.tiles_d, split, t.t[0], t.t[1], t.t[2], p,
                        mv.sh, boxes_d, fl, f, sp, float(dt), tdev, bin_start, xg, dg, plan.part_d, (int)sums,
                        plan.defer_list, plan.defer_count, mv.order_src, mv.slot_of);
   };

@@ -28,7 +28,7 @@ namespace dust {
 
 template <typename TS, typename A, int GEOM, int NDIM, bool U, bool FG>
 __global__ void __launch_bounds__(RUN_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
-    k_cells(const TileDesc* __restrict__ tiles, int TX, int TY, int TZ, PView<TS> p, ShadowView<TS> sh,
+    k_cells(const TileDesc* __restrict__ tiles, int split, int TX, int TY, int TZ, PView<TS> p, ShadowView<TS> sh,
             int clear_removed, const Box* __restrict__ boxes, FView<TS> fl, Forces f,
             const Species* __restrict__ sp, int drag_mode, A dt, const double* __restrict__ tdev,
             const int64_t* __restrict__ bin_start, const double* __restrict__ xg, DiagDev* dg,
@@ -47,10 +47,11 @@ __global__ void __launch_bounds__(RUN_THREADS) __attribute__((amdgpu_waves_per_e
   // per-species drag propagator and mass (as the tile kernel)
   __shared__ A sp_c[DUST_MAX_SPECIES], sp_psi[DUST_MAX_SPECIES], sp_m[DUST_MAX_SPECIES];
   const int tid = threadIdx.x;
-  const TileDesc td = tiles[blockIdx.x];
+  const TileDesc td = tiles[blockIdx.x / (unsigned)split];
   const Box& B = boxes[td.box];
   const int ox = td.i0 - 1, oy = td.j0 - 1, oz = td.k0 - c2;   // window origin
-  const int64_t s0 = bin_start[td.key0], s1 = bin_start[td.key0 + (int64_t)td.ex * td.ey * td.ez];
+  int64_t s0 = bin_start[td.key0], s1 = bin_start[td.key0 + (int64_t)td.ex * td.ey * td.ez];
+  if (split > 1) tile_piece(s0, s1, split);
   double s_j[3] = {0, 0, 0}, s_e = 0, s_abs = 0;
   A a_cells = A(0);
   uint32_t flags_acc = 0;
@@ -331,7 +332,8 @@ void launch_cells_g(const FusedPlan& plan, const PView<TS>& p, const FusedMove<T
                     hipStream_t st) {
   const size_t lds = cells_lds_bytes<TS, GEOM, NDIM>(plan.tile);
   auto run = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(plan.ntiles), dim3(RUN_THREADS), lds, st, plan.tiles_d, plan.tile.t[0],
+    const int split = cells_split(plan.ntiles, p.n);
+    hipLaunchKernelGGL(kern, dim3(plan.ntiles * split), dim3(RUN_THREADS), lds, st, plan.tiles_d, split, plan.tile.t[0],
                        plan.tile.t[1], NDIM > 2 ? plan.tile.t[2] : 1, p, mv.sh, mv.clear_removed, boxes_d, fl, f, sp,
                        drag_mode, A(dt), tdev, bin_start, xg, dg, plan.part_d, (int)sums, plan.defer_list,
                        plan.defer_count, mv.perm, mv.slot_of);

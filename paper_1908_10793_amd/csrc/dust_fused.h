@@ -106,13 +106,16 @@ void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, c
 // Whether a rebinning step of n particles over `cells` active cells runs a
 // particle per lane (dust_cells_kern.h) or a cell per thread.
 bool cells_path(int64_t n, int64_t cells);
+// Workgroups per tile of that kernel, which share its particles (each with a
+// window of its own): few tiles would leave CUs idle.
+int cells_split(int ntiles, int64_t n);
 
-// Adds the per-workgroup diagnostic partials of the last fused launch (tile
-// kernel and deferred kernel) to the diagnostics block, and resets the
+// Adds the per-workgroup diagnostic partials of the last fused launch (nparts
+// of the tile kernel's and the deferred kernel's) to the diagnostics block, and resets the
 // deferred-particle count; after a rebinning also fills the slots without a
 // cell (see launch_fused).
 template <typename TS>
-void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, const PView<TS>& p,
+void launch_reduce_fused(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
                          const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st);
 
 // The fused step of uniform 3-D Cartesian boxes in FP32 storage and

@@ -10,6 +10,14 @@
 
 namespace dust {
 
+// Workgroups of the particle-per-lane kernel that fill the chip: two on each
+// CU.  64^2 FP64 square, 16 tiles of some 1000 particles: 65 us with a workgroup
+// per tile, 17 with four; 32^3 shearing box, 128 tiles: 54 and 33 us with four,
+// its step 142 instead of 125 us with five (as much as 1024 workgroups ask
+// for); 48^3 FP64, 432 tiles: the step 415 us with two, 451 with five.
+static constexpr int CELLS_BLOCKS = 512;
+
+
 // Supported tile shapes (cells per axis, 256 cells each).
 struct Shape3 { int x, y, z; };
 static const Shape3 kShapes3[] = {{8, 8, 4}, {16, 4, 4}, {4, 16, 4}, {4, 4, 16}, {8, 4, 8}, {4, 8, 8}};
@@ -73,7 +81,7 @@ dust_status_t fused_plan_init(FusedPlan& plan, const Box* boxes, int nbox, TileS
   if (hipMemcpy(plan.tiles_d, tiles.data(), sizeof(TileDesc) * tiles.size(), hipMemcpyHostToDevice) !=
       hipSuccess)
     return DUST_EDEVICE;
-  if (hipMalloc((void**)&plan.part_d, sizeof(double) * PART_WORDS * (tiles.size() + DEFER_BLOCKS)) !=
+  if (hipMalloc((void**)&plan.part_d, sizeof(double) * PART_WORDS * (tiles.size() + CELLS_BLOCKS + DEFER_BLOCKS)) !=
           hipSuccess ||
       hipMalloc((void**)&plan.tile_map, 256 * tiles.size()) != hipSuccess ||
       hipMalloc((void**)&plan.defer_count, 256) != hipSuccess)
@@ -202,6 +210,7 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
   // (the deferred-particle count is zero here: set at set-up, and reset by
   // the partial reduction that ends every launch)
   if (mv.sh.rec && mv.slot_of) {
+    const int nparts = plan.ntiles * cells_split(plan.ntiles, p.n);
     if (ev0) (void)hipEventRecord(ev0, st);
 #define DUST_G(G, D, UU)                                                                                   \
   do {                                                                                                     \
@@ -211,7 +220,7 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
     hipLaunchKernelGGL((k_fused_deferred<TS, A, G, D, UU>), dim3(DEFER_BLOCKS), dim3(256), 0, st, p,       \
                        ShadowView<TS>{nullptr, nullptr}, (const uint32_t*)nullptr, boxes_d, nbox, fl, f, sp, \
                        drag_mode, A(dt), tdev, xg, (const uint32_t*)plan.defer_list,                       \
-                       (const uint32_t*)plan.defer_count, part, plan.ntiles, (int)sums, dg);               \
+                       (const uint32_t*)plan.defer_count, part, nparts, (int)sums, dg);                    \
   } while (0)
     if (geom == GEOM_CART && ndim == 2 && unif) DUST_G(GEOM_CART, 2, true);
     else if (geom == GEOM_CART && ndim == 2) DUST_G(GEOM_CART, 2, false);
@@ -220,7 +229,7 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
     else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
     else DUST_G(GEOM_SPH, 3, false);
 #undef DUST_G
-    launch_reduce_fused<TS>(plan, dg, sums, p, mv, bin_start, st);
+    launch_reduce_fused<TS>(plan, nparts, dg, sums, p, mv, bin_start, st);
     return;
   }
 #define DUST_G(G, D, UU)                                                                          \
@@ -234,15 +243,15 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
   else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
   else DUST_G(GEOM_SPH, 3, false);
 #undef DUST_G
-  launch_reduce_fused<TS>(plan, dg, sums, p, mv, bin_start, st);
+  launch_reduce_fused<TS>(plan, plan.ntiles, dg, sums, p, mv, bin_start, st);
 }
 
 template <typename TS>
-void launch_reduce_fused(const FusedPlan& plan, DiagDev* dg, bool sums, const PView<TS>& p,
+void launch_reduce_fused(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
                          const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st) {
   if (plan.ntiles == 0) return;
   hipLaunchKernelGGL((k_reduce_fused_partials<TS>), dim3(mv.sh.rec ? 1 + REDUCE_TAIL_BLOCKS : 1),
-                     dim3(REDUCE_THREADS), 0, st, (const double*)plan.part_d, plan.ntiles + DEFER_BLOCKS, dg,
+                     dim3(REDUCE_THREADS), 0, st, (const double*)plan.part_d, nparts + DEFER_BLOCKS, dg,
                      (int)sums, plan.defer_count, p, mv, bin_start);
 }
 
@@ -352,6 +361,12 @@ void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, c
 
 bool cells_path(int64_t n, int64_t cells) { return n <= CELLS_PPC * cells; }
 
+int cells_split(int ntiles, int64_t n) {
+  if (ntiles <= 0) return 1;
+  const int64_t fill = (CELLS_BLOCKS + ntiles - 1) / ntiles, chunks = (n + (int64_t)ntiles * 256 - 1) / ((int64_t)ntiles * 256);
+  return (int)std::max<int64_t>(1, std::min(fill, chunks));
+}
+
 #define DUST_FUSED_INST(TS, A)                                                                    \
   template void launch_fused<TS, A>(const FusedPlan&, const PView<TS>&, const FusedMove<TS>&,       \
                                     const Box*, int, int, int, int, const FView<TS>&,              \
@@ -366,9 +381,9 @@ DUST_FUSED_INST(float, double)
 DUST_FUSED_INST(float, float)
 DUST_FUSED_INST(double, double)
 
-template void launch_reduce_fused<float>(const FusedPlan&, DiagDev*, bool, const PView<float>&,
+template void launch_reduce_fused<float>(const FusedPlan&, int, DiagDev*, bool, const PView<float>&,
                                          const FusedMove<float>&, const int64_t*, hipStream_t);
-template void launch_reduce_fused<double>(const FusedPlan&, DiagDev*, bool, const PView<double>&,
+template void launch_reduce_fused<double>(const FusedPlan&, int, DiagDev*, bool, const PView<double>&,
                                           const FusedMove<double>&, const int64_t*, hipStream_t);
 
 }  // namespace dust

@@ -39,6 +39,19 @@ template <typename A, int NDIM> struct RunSums {
   static constexpr int WORDS = (RUN_THREADS / 64) * WR * RS;
 };
 
+// The calling workgroup's piece of its tile's particles [s0, s1), whole chunks
+// of RUN_THREADS: piece blockIdx.x mod split of `split` (the last ones may be
+// empty, s0 >= s1).
+template <typename I> __device__ __forceinline__ void tile_piece(I& s0, I& s1, int split) {
+  if (s0 >= s1) return;
+  const uint32_t chunks = (uint32_t)((s1 - s0 + RUN_THREADS - 1) / RUN_THREADS);
+  const uint32_t per = (chunks + split - 1) / split, q = blockIdx.x % (unsigned)split;
+  const uint32_t a = q * per;
+  const I end = s1;
+  s0 = a < chunks ? s0 + (I)a * RUN_THREADS : end;
+  s1 = end - s0 < (I)per * RUN_THREADS ? end : s0 + (I)per * RUN_THREADS;
+}
+
 // A wave's LDS writes before this, its reads after (its LDS operations
 // complete in order; this keeps the compiler's order).
 __device__ __forceinline__ void wave_lds_fence() {
