@@ -11,10 +11,10 @@
 namespace dust {
 
 // Workgroups of the particle-per-lane kernel that fill the chip: two on each
-// CU.  64^2 FP64 square, 16 tiles of some 1000 particles: 65 us with a workgroup
-// per tile, 17 with four; 32^3 shearing box, 128 tiles: 54 and 33 us with four,
-// its step 142 instead of 125 us with five (as much as 1024 workgroups ask
-// for); 48^3 FP64, 432 tiles: the step 415 us with two, 451 with five.
+// CU.  64^2 FP64 square of 65 k particles, 16 tiles: 65 us with a workgroup per
+// tile, 17 with sixteen.  32^3 shearing box of 262 k, 128 tiles: 54 us, 33 with
+// four, and its step 142 instead of 125 us with eight.  64^3 FP64 box of 2.1 M,
+// 1024 tiles: the step 415 us with one, 451 with two.
 static constexpr int CELLS_BLOCKS = 512;
 
 
