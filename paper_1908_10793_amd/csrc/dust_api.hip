@@ -610,12 +610,15 @@ void run_push(Ctx* c, const PView<TS>& pv, const Forces& F, double dt, int phase
     launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dg, st);
 }
 
-// After a step's particles: grid sums, fold, feedback, and the end of the step.
+// After a step's particles: what is left of a fused launch (fe), grid sums,
+// fold, feedback, and the end of the step.
 template <typename TS>
-void end_step(Ctx* c, const FView<TS>& fv, const Forces& F, double dt, int flags, hipStream_t st) {
+void end_step(Ctx* c, const FView<TS>& fv, const Forces& F, double dt, int flags, const FusedEnd<TS>& fe,
+              hipStream_t st) {
   DiagDev* dg = (flags & DUST_STEP_DIAG) ? c->diag : nullptr;
   StepEnd end{c->grid_part, 0, dg, c->tdev, dt};
-  if (dg) end.nparts = launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, st);
+  if (dg) end.nparts = launch_grid_sums<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, dg, c->grid_part, fe, st);
+  else launch_fused_end<TS>(fe, st);
   launch_fold<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, flags & DUST_STEP_APPLY_FEEDBACK, st);
   launch_finish<TS>(c->boxes.data(), c->nbox, c->boxes_d, fv, &end, st);
 }
@@ -660,7 +663,7 @@ void unfused_step(Ctx* c, const PView<TS>& pv, const FView<TS>& fv, const Forces
       launch_deposit<TS, A, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, fv, cimp, dflags, st);
     launch_drift<TS, A>(pv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif, F, 0.5 * dt, c->tdev, dt, 0, dflags, st);
   }
-  end_step<TS>(c, fv, F, dt, flags, st);
+  end_step<TS>(c, fv, F, dt, flags, FusedEnd<TS>{}, st);
 }
 
 // Whether a fused step runs the FP32 uniform-Cartesian tile kernel
@@ -726,6 +729,7 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
   }
   launch_prepare<TS>(c->boxes.data(), c->nbox, c->boxes_d, F, c->tdev, 0.5 * dt, fv, !(flags & DUST_STEP_NO_FILL),
                      c->xg, nc + 1, c->n_stored, st);
+  FusedEnd<TS> fe{};
   const bool prof = c->prof_used < c->prof_max;
   hipEvent_t ev0 = prof ? c->prof_ev[2 * c->prof_used] : nullptr;
   hipEvent_t ev1 = prof ? c->prof_ev[2 * c->prof_used + 1] : nullptr;
@@ -733,15 +737,15 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
     if (c3)
       launch_c3(c->plan, pv, mv, c->boxes_d, c->nbox, fv, F, c->species_d, c->drag_mode, dt,
                 c->tdev, c->bin_start, (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr,
-                ev0, ev1, st);
+                fe, ev0, ev1, st);
   }
   if (!c3)
     launch_fused<TS, A>(c->plan, pv, mv, c->boxes_d, c->nbox, c->geom, c->ndim, c->unif,
                         fv, F, c->species_d, c->drag_mode, dt, c->tdev, c->bin_start,
-                        (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr, ev0, ev1, st);
+                        (flags & DUST_STEP_NO_FILL) ? nullptr : c->xg, c->diag, dg != nullptr, fe, ev0, ev1, st);
   HIP_TRY(hipGetLastError());
   if (prof) ++c->prof_used;
-  end_step<TS>(c, fv, F, dt, flags, st);
+  end_step<TS>(c, fv, F, dt, flags, fe, st);
   return DUST_OK;
 }
 

@@ -149,7 +149,7 @@ size_t c3_lds_bytes(const FusedPlan& plan) {
 void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv,
                const Box* boxes_d, int nbox, const FView<float>& fl, const Forces& f, const Species* sp,
                int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
-               DiagDev* dg, bool sums, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
+               DiagDev* dg, bool sums, FusedEnd<float>& fe, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   if (plan.ntiles == 0) return;
   if (ev0) (void)hipEventRecord(ev0, st);
 #define DUST_C3(TX, TY, TZ)                                                                             \
@@ -173,7 +173,7 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
                      p, cells ? ShadowView<float>{nullptr, nullptr} : mv.sh, mv.src_index, boxes_d, nbox, fl, f, sp, drag_mode, float(dt), tdev, xg,
                      (const uint32_t*)plan.defer_list, (const uint32_t*)plan.defer_count, plan.part_d,
                      nparts, (int)sums, dg);
-  launch_reduce_fused<float>(plan, nparts, dg, sums, p, mv, bin_start, st);
+  fe = fused_end<float>(plan, nparts, dg, sums, p, mv, bin_start);
 }
 
 void launch_c3_aux(const FusedPlan& plan, const PView<float>& p, const Box* boxes_d, int nbox,

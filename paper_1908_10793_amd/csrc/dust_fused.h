@@ -82,12 +82,31 @@ template <typename TS> struct FusedMove {
   int64_t nbins;
   int clear_removed;
 };
+// What is left of a fused launch (a launch_fused or launch_c3, which fill it
+// in): the per-workgroup diagnostic partials (tile kernel and deferred
+// kernel) to be added to the diagnostics block and the deferred-particle
+// count to be reset, by one workgroup, and after a rebinning the slots without
+// a cell to be filled (see launch_fused), by tail_blocks more.  A step that
+// sums over its grid does it in that launch (launch_grid_sums), else
+// launch_fused_end.
+template <typename TS> struct FusedEnd {
+  const double* part;
+  int nparts;
+  DiagDev* dg;
+  int sums;
+  uint32_t* defer_count;
+  PView<TS> p;
+  FusedMove<TS> mv;
+  const int64_t* bin_start;
+  int tail_blocks;
+  int blocks() const { return nparts > 0 ? 1 + tail_blocks : 0; }
+};
 template <typename TS, typename A>
 void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv,
                   const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
                   const Forces& f, const Species* sp, int drag_mode, double dt, const double* tdev,
                   const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums,
-                  hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
+                  FusedEnd<TS>& fe, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
 
 // A rebinning's first pass: keys (tile-major) of the cells the particles
 // reach in the first half drift of a step of length dt starting at *tdev, and
@@ -110,13 +129,10 @@ bool cells_path(int64_t n, int64_t cells);
 // window of its own): few tiles would leave CUs idle.
 int cells_split(int ntiles, int64_t n);
 
-// Adds the per-workgroup diagnostic partials of the last fused launch (nparts
-// of the tile kernel's and the deferred kernel's) to the diagnostics block, and resets the
-// deferred-particle count; after a rebinning also fills the slots without a
-// cell (see launch_fused).
+template <typename TS> void launch_fused_end(const FusedEnd<TS>& fe, hipStream_t st);
 template <typename TS>
-void launch_reduce_fused(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
-                         const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st);
+FusedEnd<TS> fused_end(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
+                       const FusedMove<TS>& mv, const int64_t* bin_start);
 
 // The fused step of uniform 3-D Cartesian boxes in FP32 storage and
 // arithmetic (dust_cart3.hip), with forces none, constant or standard
@@ -125,7 +141,7 @@ void launch_reduce_fused(const FusedPlan& plan, int nparts, DiagDev* dg, bool su
 void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv,
                const Box* boxes_d, int nbox, const FView<float>& fl, const Forces& f, const Species* sp,
                int drag_mode, double dt, const double* tdev, const int64_t* bin_start, const double* xg,
-               DiagDev* dg, bool sums, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
+               DiagDev* dg, bool sums, FusedEnd<float>& fe, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st);
 // The same after a rebinning with a particle per lane (dust_cart3_cells.hip).
 void launch_c3_cells(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv, const Box* boxes_d,
                      const FView<float>& fl, const Forces& f, const Species* sp, double dt, const double* tdev,

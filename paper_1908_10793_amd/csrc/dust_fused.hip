@@ -127,68 +127,13 @@ size_t fused_lds_bytes(const FusedPlan& plan, int nc, int ts_bytes) {
   return fused_dep_doubles(plan.lds_cells, nc) * sizeof(double) + plan.lds_cells * 4 * (size_t)ts_bytes;
 }
 
-// Adds the per-workgroup partials of one fused launch to the diagnostics
-// block, in a fixed order (one workgroup).  After a rebinning further
-// workgroups put the packed particles without a cell in the slots from
-// bin_start[nbins] on, which no tile visits (it is usually none).
+// A fused launch's end in a launch of its own (see FusedEnd).
 static constexpr int REDUCE_THREADS = 1024;
 static constexpr int REDUCE_TAIL_BLOCKS = 31;
 template <typename TS>
-__global__ void __launch_bounds__(REDUCE_THREADS)
-    k_reduce_fused_partials(const double* __restrict__ part, int n, DiagDev* dg, int sums,
-                            uint32_t* defer_count, PView<TS> p, FusedMove<TS> mv,
-                            const int64_t* __restrict__ bin_start) {
-  if (blockIdx.x > 0) {
-    for (int64_t s = bin_start[mv.nbins] + (int64_t)(blockIdx.x - 1) * REDUCE_THREADS + threadIdx.x; s < p.n;
-         s += (int64_t)REDUCE_TAIL_BLOCKS * REDUCE_THREADS)
-      unpack_particle(mv.sh, mv.perm[s], p, s);
-    return;
-  }
-  constexpr int NW = REDUCE_THREADS / 64;
-  static_assert(REDUCE_THREADS % PART_WORDS == 0 && 64 % PART_WORDS == 0, "word per lane");
-  __shared__ double wred[NW][PART_WORDS];
-  __shared__ double red[1][PART_WORDS];
-  // the partials read as one flat array (coalesced): every element a thread
-  // reads is word k = threadIdx.x % PART_WORDS of some slot; fixed order
-  const int k = threadIdx.x % PART_WORDS;
-  const bool is_max = k == 5;
-  const int64_t total = (int64_t)n * PART_WORDS;
-  double acc = 0.0;
-#pragma unroll 8
-  for (int64_t e = threadIdx.x; e < total; e += REDUCE_THREADS) {
-    const double v = part[e];
-    acc = is_max ? fmax(acc, v) : acc + v;
-  }
-  // lanes of the wave with the same word, in a fixed butterfly
-  for (int off = PART_WORDS; off < 64; off <<= 1) {
-    const double o = __shfl_xor(acc, off);
-    acc = is_max ? fmax(acc, o) : acc + o;
-  }
-  if ((threadIdx.x & 63) < PART_WORDS) wred[threadIdx.x >> 6][k] = acc;
-  __syncthreads();
-  if (threadIdx.x < PART_WORDS) {
-    double v = wred[0][k];
-    for (int w = 1; w < NW; ++w) v = is_max ? fmax(v, wred[w][k]) : v + wred[w][k];
-    red[0][k] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (dg && sums) {
-      for (int k = 0; k < 3; ++k) dg->p_part[k] += red[0][k];
-      dg->e_part += red[0][3];
-      dg->sum_abs_j += red[0][4];
-      atomic_max_nonneg(&dg->max_cells_bits, red[0][5]);
-      if (red[0][5] > 1.8) atomicOr(&dg->flags, (unsigned)DUST_FLAG_CFL);
-    }
-    const unsigned long long fb = (unsigned long long)red[0][6];
-    if (dg && fb) {
-      dg->n_fallback += fb;
-      atomicOr(&dg->flags, (unsigned)DUST_FLAG_TILE_OVERFLOW);
-    }
-    *defer_count = 0u;   // ready for the next launch (zeroed at set-up too)
-  }
+__global__ void __launch_bounds__(REDUCE_THREADS) k_fused_end(FusedEnd<TS> fe) {
+  fused_end_block<TS, REDUCE_THREADS>(fe, blockIdx.x);
 }
-
 
 DUST_FUSED_G_ALL(extern, float, double)
 DUST_FUSED_G_ALL(extern, float, float)
@@ -203,7 +148,7 @@ static constexpr int64_t CELLS_PPC = 24;
 template <typename TS, typename A>
 void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
                   const Forces& f, const Species* sp, int drag_mode, double dt, const double* tdev,
-                  const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums,
+                  const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, FusedEnd<TS>& fe,
                   hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   if (plan.ntiles == 0) return;
   double* part = plan.part_d;
@@ -229,7 +174,7 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
     else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
     else DUST_G(GEOM_SPH, 3, false);
 #undef DUST_G
-    launch_reduce_fused<TS>(plan, nparts, dg, sums, p, mv, bin_start, st);
+    fe = fused_end<TS>(plan, nparts, dg, sums, p, mv, bin_start);
     return;
   }
 #define DUST_G(G, D, UU)                                                                          \
@@ -243,16 +188,18 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
   else if (geom == GEOM_CYL) DUST_G(GEOM_CYL, 3, false);
   else DUST_G(GEOM_SPH, 3, false);
 #undef DUST_G
-  launch_reduce_fused<TS>(plan, plan.ntiles, dg, sums, p, mv, bin_start, st);
+  fe = fused_end<TS>(plan, plan.ntiles, dg, sums, p, mv, bin_start);
 }
 
 template <typename TS>
-void launch_reduce_fused(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
-                         const FusedMove<TS>& mv, const int64_t* bin_start, hipStream_t st) {
-  if (plan.ntiles == 0) return;
-  hipLaunchKernelGGL((k_reduce_fused_partials<TS>), dim3(mv.sh.rec ? 1 + REDUCE_TAIL_BLOCKS : 1),
-                     dim3(REDUCE_THREADS), 0, st, (const double*)plan.part_d, nparts + DEFER_BLOCKS, dg,
-                     (int)sums, plan.defer_count, p, mv, bin_start);
+FusedEnd<TS> fused_end(const FusedPlan& plan, int nparts, DiagDev* dg, bool sums, const PView<TS>& p,
+                       const FusedMove<TS>& mv, const int64_t* bin_start) {
+  return {plan.part_d, nparts + DEFER_BLOCKS, dg, (int)sums, plan.defer_count, p, mv, bin_start,
+          mv.sh.rec ? REDUCE_TAIL_BLOCKS : 0};
+}
+
+template <typename TS> void launch_fused_end(const FusedEnd<TS>& fe, hipStream_t st) {
+  if (fe.blocks() > 0) hipLaunchKernelGGL((k_fused_end<TS>), dim3(fe.blocks()), dim3(REDUCE_THREADS), 0, st, fe);
 }
 
 // ---------------------------------------------------------------- rebinning by half-step cell
@@ -371,8 +318,8 @@ int cells_split(int ntiles, int64_t n) {
   template void launch_fused<TS, A>(const FusedPlan&, const PView<TS>&, const FusedMove<TS>&,       \
                                     const Box*, int, int, int, int, const FView<TS>&,              \
                                     const Forces&, const Species*, int, double, const double*,     \
-                                    const int64_t*, const double*, DiagDev*, bool, hipEvent_t,     \
-                                    hipEvent_t, hipStream_t);                                      \
+                                    const int64_t*, const double*, DiagDev*, bool, FusedEnd<TS>&,  \
+                                    hipEvent_t, hipEvent_t, hipStream_t);                          \
   template void launch_halfstep_keys<TS, A>(const PView<TS>&, const Box*, int, int, int, int,       \
                                             const Forces&, double, const double*, int64_t,         \
                                             TileShape, uint32_t*, const ShadowView<TS>&, hipStream_t);
@@ -381,9 +328,9 @@ DUST_FUSED_INST(float, double)
 DUST_FUSED_INST(float, float)
 DUST_FUSED_INST(double, double)
 
-template void launch_reduce_fused<float>(const FusedPlan&, int, DiagDev*, bool, const PView<float>&,
-                                         const FusedMove<float>&, const int64_t*, hipStream_t);
-template void launch_reduce_fused<double>(const FusedPlan&, int, DiagDev*, bool, const PView<double>&,
-                                          const FusedMove<double>&, const int64_t*, hipStream_t);
+template FusedEnd<float> fused_end<float>(const FusedPlan&, int, DiagDev*, bool, const PView<float>&,
+                                         const FusedMove<float>&, const int64_t*);
+template void launch_fused_end<float>(const FusedEnd<float>&, hipStream_t);
+template void launch_fused_end<double>(const FusedEnd<double>&, hipStream_t);
 
 }  // namespace dust

@@ -201,6 +201,62 @@ __device__ __forceinline__ void unpack_particle(const ShadowView<TS>& sh, int64_
   }
 }
 
+// Workgroup blk of a FusedEnd: 0 adds the partials to the diagnostics block in
+// a fixed order, the others fill the slots without a cell (usually none).
+template <typename TS, int THREADS>
+__device__ __forceinline__ void fused_end_block(const FusedEnd<TS>& fe, unsigned blk) {
+  if (blk > 0) {
+    for (int64_t s = fe.bin_start[fe.mv.nbins] + (int64_t)(blk - 1) * THREADS + threadIdx.x; s < fe.p.n;
+         s += (int64_t)fe.tail_blocks * THREADS)
+      unpack_particle(fe.mv.sh, fe.mv.perm[s], fe.p, s);
+    return;
+  }
+  constexpr int NW = THREADS / 64;
+  static_assert(THREADS % PART_WORDS == 0 && 64 % PART_WORDS == 0, "word per lane");
+  __shared__ double wred[NW][PART_WORDS];
+  __shared__ double red[PART_WORDS];
+  // the partials read as one flat array (coalesced): every element a thread
+  // reads is word k = threadIdx.x % PART_WORDS of some slot; fixed order
+  const int k = threadIdx.x % PART_WORDS;
+  const bool is_max = k == 5;
+  const int64_t total = (int64_t)fe.nparts * PART_WORDS;
+  double acc = 0.0;
+#pragma unroll 16
+  for (int64_t e = threadIdx.x; e < total; e += THREADS) {
+    const double v = fe.part[e];
+    acc = is_max ? fmax(acc, v) : acc + v;
+  }
+  // lanes of the wave with the same word, in a fixed butterfly
+  for (int off = PART_WORDS; off < 64; off <<= 1) {
+    const double o = __shfl_xor(acc, off);
+    acc = is_max ? fmax(acc, o) : acc + o;
+  }
+  if ((threadIdx.x & 63) < PART_WORDS) wred[threadIdx.x >> 6][k] = acc;
+  __syncthreads();
+  if (threadIdx.x < PART_WORDS) {
+    double v = wred[0][k];
+    for (int w = 1; w < NW; ++w) v = is_max ? fmax(v, wred[w][k]) : v + wred[w][k];
+    red[k] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    DiagDev* dg = fe.dg;
+    if (dg && fe.sums) {
+      for (int q = 0; q < 3; ++q) dg->p_part[q] += red[q];
+      dg->e_part += red[3];
+      dg->sum_abs_j += red[4];
+      atomic_max_nonneg(&dg->max_cells_bits, red[5]);
+      if (red[5] > 1.8) atomicOr(&dg->flags, (unsigned)DUST_FLAG_CFL);
+    }
+    const unsigned long long fb = (unsigned long long)red[6];
+    if (dg && fb) {
+      dg->n_fallback += fb;
+      atomicOr(&dg->flags, (unsigned)DUST_FLAG_TILE_OVERFLOW);
+    }
+    *fe.defer_count = 0u;   // ready for the next launch (zeroed at set-up too)
+  }
+}
+
 // Register budget: the FP32 kernel needs about 250 VGPRs (108 of them the
 // register sums); the compiler keeps the standard-form shapes but one under
 // 256 (2 waves/SIMD) by itself, and 4x4x16, the orbital-advection and the
@@ -975,10 +1031,6 @@ void launch_fused_g(const FusedPlan& plan, const PView<TS>& p, const FusedMove<T
       const Forces&, const Species*, int, double, const double*, const int64_t*, const double*,       \
       DiagDev*, double*, bool, uint32_t*, uint32_t*, int, hipEvent_t, hipEvent_t,                      \
       hipStream_t);
-#define DUST_DEFERRED_DECL(PREFIX, TS, A, G, D, UU)                                                     \
-  PREFIX template __global__ void k_fused_deferred<TS, A, G, D, UU>(                                  \
-      PView<TS>, ShadowView<TS>, const uint32_t*, const Box*, int, FView<TS>, Forces, const Species*, \
-      int, A, const double*, const double*, const uint32_t*, const uint32_t*, double*, int, int, DiagDev*);
 #define DUST_FUSED_G_ALL(PREFIX, TS, A)                                                                \
   DUST_FUSED_G_DECL(PREFIX, TS, A, GEOM_CART, 2, true)                                                 \
   DUST_FUSED_G_DECL(PREFIX, TS, A, GEOM_CART, 2, false)                                                \

@@ -108,12 +108,14 @@ template <typename TS>
 void launch_feedback(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, hipStream_t st);
 // FP64 grid sums of the boxes; part: GRID_SUM_PARTS * 4 doubles of scratch.
 // Returns the number of partials in it that launch_finish is to add to dg
-// (those of earlier launches of many boxes are added on the way).
+// (those of earlier launches of many boxes are added on the way).  fe: what is
+// left of the step's fused launch (or empty), done in the same launch.
+template <typename TS> struct FusedEnd;
 static constexpr int GRID_SUM_BLOCKS = 2048;
 static constexpr int GRID_SUM_PARTS = GRID_SUM_BLOCKS + 16;
 template <typename TS>
 int launch_grid_sums(const Box* hb, int nbox, const Box* boxes_d, const FView<TS>& fl, DiagDev* dg, double* part,
-                     hipStream_t st);
+                     const FusedEnd<TS>& fe, hipStream_t st);
 template <typename TS> void launch_fill_value(TS* a, int64_t n, TS v, hipStream_t st);
 
 // Binning (dust_bin.hip).  Workspace sizes in bytes for n particles.
