@@ -14,7 +14,7 @@
 
 namespace dust {
 
-template <bool SB, bool SMALL>
+template <bool SB, int BOXES>
 __global__ void __launch_bounds__(RUN_THREADS)
     k_c3_cells(const TileDesc* __restrict__ tiles, int split, int TX, int TY, int TZ, PView<float> p, ShadowView<float> sh,
                const Box* __restrict__ boxes, FView<float> fl, Forces f, const Species* __restrict__ sp, float dt,
@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(RUN_THREADS)
     }
     const double t0 = *tdev;
     const int n0 = cb.n[0], n1 = cb.n[1], n2 = cb.n[2];
-    const bool small = SMALL || cb.ncell < (1 << 24);
+    const bool small = BOXES >= C3_SMALL || cb.ncell < (1 << 24);
     // the first particles are on their way while the window is staged; then
     // each chunk's are loaded one chunk ahead, their places two (past the
     // last: the last one again, not used)
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(RUN_THREADS)
       int32_t ncell = -1;
       if (live) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) c3_weights(cb.tsc[d], off[d], st.w[d]);
+        for (int d = 0; d < 3; ++d) c3_weights<BOXES == C3_TSC>(cb.tsc[d], off[d], st.w[d]);
         // gather (Eq. Delta_vp), one z-plane of the stencil at a time
         float v[3] = {0.0f, 0.0f, 0.0f};
         int rr = r0 - RX * RY - RX;
@@ -340,12 +340,15 @@ void launch_c3_cells(const FusedPlan& plan, const PView<float>& p, const FusedMo
                        plan.defer_list, plan.defer_count, mv.order_src, mv.slot_of);
   };
   const bool sb = f.kind == FORCE_SHEARBOX;
-  if (plan.small) {
-    if (sb) run(k_c3_cells<true, true>);
-    else run(k_c3_cells<false, true>);
+  if (plan.small && plan.tsc) {
+    if (sb) run(k_c3_cells<true, C3_TSC>);
+    else run(k_c3_cells<false, C3_TSC>);
+  } else if (plan.small) {
+    if (sb) run(k_c3_cells<true, C3_SMALL>);
+    else run(k_c3_cells<false, C3_SMALL>);
   } else {
-    if (sb) run(k_c3_cells<true, false>);
-    else run(k_c3_cells<false, false>);
+    if (sb) run(k_c3_cells<true, C3_ANY>);
+    else run(k_c3_cells<false, C3_ANY>);
   }
 }
 

@@ -36,12 +36,11 @@ namespace dust {
 // [-1/2, 1/2)); returns the new cell index (not wrapped).  Without branches
 // (a wave takes a branch whenever one of its lanes crosses a face): the
 // nearest integer k splits the new offset d exactly (d - k is exact in FP32
-// for |d| < 2^23), a tie at +1/2 goes to the next cell, and an offset that
-// stays in its cell is kept as it is.
+// for |d| < 2^23), and a tie at +1/2 goes to the next cell.
 __device__ __forceinline__ int c3_move(int i, float& off, float v, float hinv) {
   const float dn = fmaf(v, hinv, off);
   const float k = rintf(dn);
-  const float r0 = k == 0.0f ? dn : dn - k;
+  const float r0 = dn - k;
   const bool up = r0 >= 0.5f;
   off = up ? r0 - 1.0f : r0;
   return i + (int)k + (up ? 1 : 0);
@@ -78,6 +77,8 @@ __device__ __forceinline__ void c3_unravel(int l, int n0, int n1, double inv0, d
 __device__ __forceinline__ void c3_unravel(int l, int n0, int n1, double inv0, double inv1, int idx[3]) {
   c3_unravel(l, n0, n1, inv0, inv1, idx, l < (1 << 24) && n0 < (1 << 24) && n1 < (1 << 24));
 }
+
+enum { C3_ANY = 0, C3_SMALL = 1, C3_TSC = 2 };
 
 // Uniform constants of the workgroup's box.
 struct C3Box {
@@ -118,7 +119,20 @@ __device__ __forceinline__ int32_t c3_cell_id(const C3Box& cb, int i, int j, int
 
 // Weights of cells i-1, i, i+1 of one axis (b-spline overlaps, Eq. b0 / b1),
 // middle weight 1 - w0 - w2.
+// (ALL_TSC: of every axis, known at compile time: the same values.  The tile
+// kernel is bound by its VALU, 773 instructions per 64 particles of which these
+// and the two moves were 60: 3.03 ms a step for 121 M particles on stale bins
+// with the blends, 2.86 without.)
+template <bool ALL_TSC = false>
 __device__ __forceinline__ void c3_weights(bool tsc, float d, float w[3]) {
+  if constexpr (ALL_TSC) {
+#pragma clang fp contract(off)   // (the middle weight from the rounded outer ones)
+    const float m = 0.5f - d, p = 0.5f + d;
+    w[0] = 0.5f * m * m;
+    w[2] = 0.5f * p * p;
+    w[1] = 1.0f - w[0] - w[2];
+    return;
+  }
   // both forms, blended by t = 1 (TSC) or 0 (CIC): t a + (1 - t) b is a or b
   // exactly, and no branch on the box's shape
   const float t = tsc ? 1.0f : 0.0f, u = 1.0f - t;
@@ -259,12 +273,14 @@ __device__ __forceinline__ void c3_spill_planes(double* dep, int base, int sx, i
 }
 
 // The fused step.  SB: standard shearing-box forces (else none or a constant
-// acceleration).  SMALL: every box of the launch has fewer than 2^24 cells.  
+// acceleration).  BOXES: what every box of the launch is known to be when it
+// is compiled: C3_ANY nothing, C3_SMALL of fewer than 2^24 cells, C3_TSC also
+// of TSC shape on every axis.  
 // REBIN: the step after a rebinning (the packed particles read through
 // src_index and written to the arrays in binned order, attributes too, with
 // input checks); else stale bins, in place.  Masses and stopping times come
 // from the species table.
-template <int TX, int TY, int TZ, bool SB, bool REBIN, bool SMALL>
+template <int TX, int TY, int TZ, bool SB, bool REBIN, int BOXES>
 __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
     k_c3(const TileDesc* __restrict__ tiles, const uint8_t* __restrict__ tmap, PView<float> p,
          ShadowView<float> sh, const Box* __restrict__ boxes, FView<float> fl, Forces f,
@@ -364,7 +380,7 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
   const int mybase = (lx + H) + RX * ((ly + H) + RY * (lz + H));
   // boxes of fewer than 2^24 cells: FP32 division and 24-bit products (known
   // at compile time when every box of the launch is that small)
-  const bool small = SMALL || cb.ncell < (1 << 24);
+  const bool small = BOXES >= C3_SMALL || cb.ncell < (1 << 24);
   const int32_t mycid = c3_cell_id(cb, mycell[0], mycell[1], mycell[2], small);
 
   float acc[27][4];
@@ -451,7 +467,7 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
       const int code = spq_s[wv][lane];
       float w2[3][3], q2[4];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) c3_weights(cb.tsc[d], spq_o[wv][d][lane], w2[d]);
+      for (int d = 0; d < 3; ++d) c3_weights<BOXES == C3_TSC>(cb.tsc[d], spq_o[wv][d][lane], w2[d]);
 #pragma unroll
       for (int k = 0; k < 4; ++k) q2[k] = spq_q[wv][k][lane];
       c3_spill_planes<RX, RY, RC>(dep, spq_r[wv][lane], code % 3 - 1, (code / 3) % 3 - 1, code / 9 - 1, w2, q2);
@@ -503,14 +519,9 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
         }
       }
     }
-    // a lane without a live particle drifts a particle at rest in the centre
-    // of its thread's cell (no branch around the drift)
-    float off[3], mom[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      off[d] = live ? cur.off[d] : 0.0f;
-      mom[d] = live ? cur.mom[d] : 0.0f;
-    }
+    // a lane without a live particle drifts whatever it has loaded from its
+    // thread's cell (no branch around the drift), and drops it below
+    float off[3] = {cur.off[0], cur.off[1], cur.off[2]}, mom[3] = {cur.mom[0], cur.mom[1], cur.mom[2]};
     {
       // after a rebinning every particle is in its thread's cell; on stale
       // bins some lane of a wave nearly always is not: no branch then (a box
@@ -534,7 +545,7 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
             else if (d == 0 && cb.shear) deferred = true;
             else removed = true;
           }
-        if (removed) {
+        if (removed && live) {
           // left through an open face: no cell from now on (it keeps the
           // offsets and momenta it had when it left)
           at32(out.cell, i) = -1;
@@ -585,7 +596,7 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
     // weights at x^{n+1/2}
     float w[3][3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) c3_weights(cb.tsc[d], off[d], w[d]);
+    for (int d = 0; d < 3; ++d) c3_weights<BOXES == C3_TSC>(cb.tsc[d], off[d], w[d]);
     const int sx = la - (lx + H), sy = lb - (ly + H), sz = lcz - (lz + H);
     const bool near = sx >= -1 && sx <= 1 && sy >= -1 && sy <= 1 && sz >= -1 && sz <= 1;
     // gather (Eq. Delta_vp), one z-plane of the stencil at a time: the nine
@@ -841,12 +852,12 @@ __global__ void __launch_bounds__(FUSED_THREADS) __attribute__((amdgpu_waves_per
   }
 }
 
-template <int TX, int TY, int TZ, bool SB, bool REBIN, bool SMALL>
+template <int TX, int TY, int TZ, bool SB, bool REBIN, int BOXES>
 void launch_c3_t(const FusedPlan& plan, const PView<float>& p, const FusedMove<float>& mv, const Box* boxes_d,
                  const FView<float>& fl, const Forces& f, const Species* sp, double dt, const double* tdev,
                  const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, hipStream_t st) {
   const size_t lds = c3_lds_bytes(plan);
-  auto kern = k_c3<TX, TY, TZ, SB, REBIN, SMALL>;
+  auto kern = k_c3<TX, TY, TZ, SB, REBIN, BOXES>;
   if (lds > 64 * 1024) {
     static bool raised = false;
     if (!raised) {
@@ -868,12 +879,15 @@ void launch_c3_shape(const FusedPlan& plan, const PView<float>& p, const FusedMo
                      const int64_t* bin_start, const double* xg, DiagDev* dg, bool sums, hipStream_t st) {
 #define DUST_C3M(SBV, RB)                                                                                      \
   do {                                                                                                         \
-    if (plan.small)                                                                                            \
-      launch_c3_t<TX, TY, TZ, SBV, RB, true>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,     \
-                                             sums, st);                                                        \
+    if (plan.small && plan.tsc)                                                                                \
+      launch_c3_t<TX, TY, TZ, SBV, RB, C3_TSC>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,   \
+                                               sums, st);                                                      \
+    else if (plan.small)                                                                                       \
+      launch_c3_t<TX, TY, TZ, SBV, RB, C3_SMALL>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, \
+                                                 sums, st);                                                    \
     else                                                                                                       \
-      launch_c3_t<TX, TY, TZ, SBV, RB, false>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,    \
-                                              sums, st);                                                       \
+      launch_c3_t<TX, TY, TZ, SBV, RB, C3_ANY>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg,   \
+                                               sums, st);                                                      \
   } while (0)
   const bool sb = f.kind == FORCE_SHEARBOX;
   if (mv.sh.rec) {
