@@ -24,10 +24,12 @@ namespace dust {
 static constexpr int BIN_THREADS = 256;
 static constexpr int BIN_WAVES = BIN_THREADS / 64;
 static constexpr int BIN_MAX_BITS = 9;
-// below this many keys, blocks of 1024 instead of 4096 (4096 would leave CUs idle)
-static constexpr int64_t BIN_FEW = 1 << 19;
-
-// up to this many blocks, a pass without a scan
+// Below this many keys, blocks of 1024 instead of 4096, which would leave
+// CUs idle.  A sort of random tile keys, us with 1024 and 4096: 62 and 82 at
+// 2^19 keys, 92 and 107 at 2^21, 142 and 124 at 2^22, 445 and 340 at 2^24.
+static constexpr int64_t BIN_FEW = 3 << 20;
+// Up to this many blocks, a pass without a scan: 26 and 41 us with one at 64
+// blocks, 29 and 41 at 128, 50 and 58 at 256, 65 and 60 at 384.
 static constexpr int64_t BIN_DIRECT = 256;
 
 // Sort keys from the cells, KEYS_PER particles of a thread (their loads
