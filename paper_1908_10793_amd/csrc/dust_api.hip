@@ -443,19 +443,23 @@ dust_status_t ensure_det(Ctx* c, int64_t n) {
 }
 
 // Whether a call's particle-to-grid sums run over particles sorted by tile
-// (dust_sorted.h), its workspace then in place.  The sort costs 5 launches a
-// radix pass and its window one flush a tile, so:
-//  * from 16384 particles on (a deposit of 4096 took 29 us particle by
-//    particle and 92 us sorted, one of 16384 117 and 95 us);
-//  * at one particle per active cell or more on average (below, a tile's
-//    window flush costs more than its particles' own atomics);
+// (dust_sorted.h), its workspace then in place.  The sort costs two launches
+// a radix pass at least and the windows one flush a tile that has particles,
+// so:
+//  * from 4096 particles on.  us of a deposit / drag source / density, FP32,
+//    sorted and particle by particle: 4096 in 16^3 cells 42 / 48 / 36 and
+//    58 / 139 / 58; 1728 in 12^3 42 / 48 / 36 and 49 / 114 / 22; 262144 in 32^3
+//    82 / 79 / 51 and 1508 / 1150 / 405;
+//  * at a quarter particle per active cell or more on average (8192 in 32^3
+//    63 / 76 / 52 and 68 / 164 / 61, 65536 in 64^3 78 / 89 / 63 and
+//    350 / 292 / 103; below, ever more windows are flushed for a few particles);
 //  * not while the stream is being captured by the caller: a captured call
 //    must not hold workspace that a later call may replace;
 //  * not where the workspace (24 bytes per particle) cannot be had.
 // Otherwise each particle adds to the grid by itself, as the other kernels do.
-constexpr int64_t SORTED_MIN = 16384;
+constexpr int64_t SORTED_MIN = 4096;
 bool sorted_sums(Ctx* c, int64_t n, hipStream_t st) {
-  if (n < SORTED_MIN || n < c->n_active) return false;
+  if (n < SORTED_MIN || 4 * n < c->n_active) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
@@ -713,7 +717,7 @@ dust_status_t fused_step(Ctx* c, const PView<TS>& pv, const ShadowView<TS>& sh, 
     // (the other buffers are free once the sort is done)
     uint32_t* lm = c->bin.val[1 - c->bin_cur];
     uint32_t* lm2 = c->bin.key[1 - c->bin_cur];
-    const bool cells = cells_path(pv.n, c->n_active);
+    const bool cells = cells_path(pv.n, c->n_active, c->geom, c3);
     if (c3) {
       launch_c3_level_perm(c->plan, c->bin.val[c->bin_cur], c->bin_start, lm, cells ? lm2 : nullptr, st);
       mv.order_src = cells ? lm : nullptr;

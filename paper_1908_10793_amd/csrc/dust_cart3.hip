@@ -23,7 +23,7 @@ DUST_C3_AUX_SHAPES(extern)
 // by (rank, group): a wave of a full tile takes 4 ranks of every group, and
 // every 16 consecutive lanes hold one cell of each group.  (rx, ry: x and y
 // extents of the tile kernel's gas window.)  A cell looks for its rank among
-// its group only: 32^3 box of 131 k particles 12 us (against all cells of the
+// its group only: 32^3 box of 262 k particles 12 us (against all cells of the
 // tile 32), 128^3 box of 16.8 M 128 us (175), where the writes of the pairs
 // bound it.
 __global__ void __launch_bounds__(256)
@@ -155,7 +155,7 @@ void launch_c3(const FusedPlan& plan, const PView<float>& p, const FusedMove<flo
 #define DUST_C3(TX, TY, TZ)                                                                             \
   launch_c3_shape<TX, TY, TZ>(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st)
   const bool cells = mv.sh.rec && mv.order_src;
-  const int nparts = plan.ntiles * (cells ? cells_split(plan.ntiles, p.n) : 1);
+  const int nparts = plan.ntiles * (cells ? cells_split(plan.ntiles, p.n, false) : 1);
   if (cells)
     launch_c3_cells(plan, p, mv, boxes_d, fl, f, sp, dt, tdev, bin_start, xg, dg, sums, st);
   else

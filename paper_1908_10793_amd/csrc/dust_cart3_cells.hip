@@ -334,7 +334,7 @@ void launch_c3_cells(const FusedPlan& plan, const PView<float>& p, const FusedMo
   const size_t wc = (size_t)(t.t[0] + 2) * (t.t[1] + 2) * (t.t[2] + 2);
   const size_t lds = wc * (4 * sizeof(double) + sizeof(float4)) + (size_t)(t.t[0] + 2) * sizeof(float2);
   auto run = [&](auto kern) {
-    const int split = cells_split(plan.ntiles, p.n);
+    const int split = cells_split(plan.ntiles, p.n, false);
     hipLaunchKernelGGL(kern, dim3(plan.ntiles * split), dim3(RUN_THREADS), lds, st, plan.tiles_d, split, t.t[0], t.t[1], t.t[2], p,
                        mv.sh, boxes_d, fl, f, sp, float(dt), tdev, bin_start, xg, dg, plan.part_d, (int)sums,
                        plan.defer_list, plan.defer_count, mv.order_src, mv.slot_of);

@@ -332,7 +332,7 @@ void launch_cells_g(const FusedPlan& plan, const PView<TS>& p, const FusedMove<T
                     hipStream_t st) {
   const size_t lds = cells_lds_bytes<TS, GEOM, NDIM>(plan.tile);
   auto run = [&](auto kern) {
-    const int split = cells_split(plan.ntiles, p.n);
+    const int split = cells_split(plan.ntiles, p.n, sizeof(A) == 8);
     hipLaunchKernelGGL(kern, dim3(plan.ntiles * split), dim3(RUN_THREADS), lds, st, plan.tiles_d, split, plan.tile.t[0],
                        plan.tile.t[1], NDIM > 2 ? plan.tile.t[2] : 1, p, mv.sh, mv.clear_removed, boxes_d, fl, f, sp,
                        drag_mode, A(dt), tdev, bin_start, xg, dg, plan.part_d, (int)sums, plan.defer_list,

@@ -125,10 +125,10 @@ void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, c
 
 // Whether a rebinning step of n particles over `cells` active cells runs a
 // particle per lane (dust_cells_kern.h) or a cell per thread.
-bool cells_path(int64_t n, int64_t cells);
+bool cells_path(int64_t n, int64_t cells, int geom, bool c3);
 // Workgroups per tile of that kernel, which share its particles (each with a
 // window of its own): few tiles would leave CUs idle.
-int cells_split(int ntiles, int64_t n);
+int cells_split(int ntiles, int64_t n, bool f64);
 
 template <typename TS> void launch_fused_end(const FusedEnd<TS>& fe, hipStream_t st);
 template <typename TS>

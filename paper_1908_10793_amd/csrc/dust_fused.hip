@@ -10,12 +10,9 @@
 
 namespace dust {
 
-// Workgroups of the particle-per-lane kernel that fill the chip: two on each
-// CU.  64^2 FP64 square of 65 k particles, 16 tiles: 65 us with a workgroup per
-// tile, 17 with sixteen.  32^3 shearing box of 262 k, 128 tiles: 54 us, 33 with
-// four, and its step 142 instead of 125 us with eight.  64^3 FP64 box of 2.1 M,
-// 1024 tiles: the step 415 us with one, 451 with two.
-static constexpr int CELLS_BLOCKS = 512;
+// Workgroups of the particle-per-lane kernel that the chip holds at once (its
+// LDS: three on each of 256 CUs, two with FP64 arithmetic).
+static constexpr int CELLS_BLOCKS = 768, CELLS_BLOCKS_F64 = 512;
 
 
 // Supported tile shapes (cells per axis, 256 cells each).
@@ -144,8 +141,6 @@ DUST_CELLS_ALL(extern, float, double)
 DUST_CELLS_ALL(extern, float, float)
 DUST_CELLS_ALL(extern, double, double)
 
-// Largest mean of particles per cell for the particle-per-lane kernel.
-static constexpr int64_t CELLS_PPC = 24;
 
 template <typename TS, typename A>
 void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>& mv, const Box* boxes_d, int nbox, int geom, int ndim, int unif, const FView<TS>& fl,
@@ -157,7 +152,7 @@ void launch_fused(const FusedPlan& plan, const PView<TS>& p, const FusedMove<TS>
   // (the deferred-particle count is zero here: set at set-up, and reset by
   // the partial reduction that ends every launch)
   if (mv.sh.rec && mv.slot_of) {
-    const int nparts = plan.ntiles * cells_split(plan.ntiles, p.n);
+    const int nparts = plan.ntiles * cells_split(plan.ntiles, p.n, sizeof(A) == 8);
     if (ev0) (void)hipEventRecord(ev0, st);
 #define DUST_G(G, D, UU)                                                                                   \
   do {                                                                                                     \
@@ -308,11 +303,32 @@ void launch_level_perm(const FusedPlan& plan, int64_t n, const uint32_t* perm, c
                      (int)inverse);
 }
 
-bool cells_path(int64_t n, int64_t cells) { return n <= CELLS_PPC * cells; }
+// A fused rebinning step's us with a particle per lane and a cell per thread:
+//  * 64x96x16 cylindrical disk, FP32, 136 and 200 at 4 particles per cell, 471
+//    and 624 at 32, 731 and 841 at 48, 1026 and 1056 at 64; 64x32x48 spherical
+//    disk 140 and 216, 498 and 633, 807 and 864, 1165 and 1081 (FP64: 1516 and
+//    2146 at 64);
+//  * Cartesian, where the tile kernel's arithmetic is shorter: 256^2, FP32, 105
+//    and 121 at 4, 183 and 219 at 24, 232 and 250 at 32, 402 and 322 at 48; FP64
+//    235 and 259 at 24, 357 and 328 at 32; 48^3, FP64, 184 and 243 at 4, 519 and
+//    625 at 24, 1057 and 1044 at 48;
+//  * FP32 uniform Cartesian (c3), shorter again: 96^3 525 and 581 at 4, 835 and
+//    812 at 8, 1309 and 1040 at 12; shearing boxes whose particles have gathered,
+//    at 8, 116 and 139 (32^3), 852 and 873 (100x96x72), 1472 and 1529 (128^3).
+bool cells_path(int64_t n, int64_t cells, int geom, bool c3) {
+  return n <= (c3 ? 9 : geom == GEOM_CART ? 28 : 56) * cells;
+}
 
-int cells_split(int ntiles, int64_t n) {
+// As many workgroups a tile as the chip holds at once, each with a chunk of
+// particles at least.  us with one and with more: 64^2 FP64 square of 65 k
+// particles, 16 tiles, the kernel 65 and (16) 17; 32^3 shearing box of 262 k, 128
+// tiles, 54 and (4) 33; 64x96x16 cylindrical disk at 8 per cell, FP32, 384 tiles,
+// the step 189 and (2) 167.  More than the chip holds lose: that disk in FP64 225
+// and (2) 243, 48^3 shearing box at 8 per cell, FP32, 432 tiles, 205 and (2) 224.
+int cells_split(int ntiles, int64_t n, bool f64) {
   if (ntiles <= 0) return 1;
-  const int64_t fill = (CELLS_BLOCKS + ntiles - 1) / ntiles, chunks = (n + (int64_t)ntiles * 256 - 1) / ((int64_t)ntiles * 256);
+  const int64_t fill = (f64 ? CELLS_BLOCKS_F64 : CELLS_BLOCKS) / ntiles,
+                chunks = (n + (int64_t)ntiles * 256 - 1) / ((int64_t)ntiles * 256);
   return (int)std::max<int64_t>(1, std::min(fill, chunks));
 }
 

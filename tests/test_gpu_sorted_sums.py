@@ -1,7 +1,7 @@
 """The particle-to-grid sums over sorted particles (deposit stage, drag
 source, dust density) against the same calls on slices of the particles.
 
-A call of 16384 particles or more, with at least one per cell, sorts the
+A call of 4096 particles or more, with a quarter per cell or more, sorts the
 particles and sums them tile by tile; a slice below that size adds particle
 by particle.  Both are the same sums, so the whole call must equal the sum of
 its slices.  Tolerances (normwise, per channel): FP64 contributions and sums
@@ -17,14 +17,14 @@ from paper_1908_10793_amd import synth
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-SLICE = 16000   # below the sorted path's smallest call
+SLICE = 4000   # below the sorted path's smallest call
 
 
 def _workload(name, dtype):
     kw = dict(dtype=dtype)
     if name == "square_ragged":      # 2-D tiles with remainders on both axes
         return synth.cart2d_periodic(n=(33, 50), ppc=10, shape="cic", **kw)
-    if name == "square_smallest":    # exactly the smallest sorted call: one tile
+    if name == "square_smallest":    # one tile
         return synth.cart2d_periodic(n=(16, 16), ppc=64, shape="tsc", **kw)
     if name == "box_thin":           # fewer cells than a tile along two axes
         return synth.shearing_box(n=(700, 3, 2), **kw)
