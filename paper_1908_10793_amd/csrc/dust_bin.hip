@@ -362,7 +362,9 @@ static BinPlan bin_plan(int64_t n, int64_t nbins, size_t hist_words) {
 size_t bin_hist_words(int64_t n, bool fixed) {
   const size_t least = (size_t)256 * ceil_div(n, BIN_THREADS * 16);
   if (fixed) return least;
-  return std::max(least, (size_t)ceil_div(n, BIN_THREADS * (n >= BIN_FEW ? 16 : 4)) << BIN_MAX_BITS);
+  // (also for fewer keys later, in their smaller blocks)
+  const size_t few = (size_t)ceil_div(std::min(n, BIN_FEW), BIN_THREADS * 4) << BIN_MAX_BITS;
+  return std::max({least, few, (size_t)ceil_div(n, BIN_THREADS * 16) << BIN_MAX_BITS});
 }
 
 size_t bin_scan_tmp_words(int64_t m) {

@@ -6,9 +6,10 @@
 // The workgroup walks its tile's particles cell by cell in the order in which
 // the layout hands the cells to lanes (order_src, order_slot of
 // k_c3_level_perm), so that the lanes of a wave write stretches of a level.
-// 128^3 shearing box, 8 particles per cell, 8x8x4 tiles: the tile kernel of
-// dust_cart3_kern.h takes 920 us after a rebinning (its window staging and its
-// 2 waves per SIMD weigh most at so few particles per thread).
+// 128^3 shearing box, 8 particles per cell: 734 us, its VALU busy for 460 (1070
+// instructions per 64 particles) and its LDS for 480 (the gather's reads 330,
+// the sums by runs most of the rest); with the tile kernel of dust_cart3_kern.h
+// the whole step takes 1529 us instead of 1472.
 #include "dust_cart3_kern.h"
 #include "dust_runsum.h"
 

@@ -113,8 +113,8 @@ __device__ __forceinline__ uint32_t level_slot(const WaveLevels& w, int j, uint3
 
 // Raw stored state of one particle (prefetched one particle ahead), with the
 // attributes the kick reads (species, mass, drag: each only if present) and,
-// when the attributes are copied to another buffer, the id: no load of the
-// loop's body waits on memory.
+// when the attributes are written too (after a rebinning), the id: no load of
+// the loop's body waits on memory.
 template <typename TS> struct Raw {
   int32_t cell;
   TS off[3], mom[3];
