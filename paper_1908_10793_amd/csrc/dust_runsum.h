@@ -123,7 +123,7 @@ __device__ __forceinline__ void run_sums(double* win, int RX, int RY, int WC, A*
     // FP32: a run that ended waits in `done` until some group's next one ends,
     // or the last particle: the groups' runs end at different particles, and
     // the adds of one wave cost the same for one group as for seven.  128^3
-    // box at 8 particles per cell: 771 -> 725 us.  (FP64 lacks the registers:
+    // box at 8 particles per cell: 771 -> 734 us.  (FP64 lacks the registers:
     // the drag source of 14 M particles took 1592 us so, 1353 without.)
     A acc[NA][NCH], done[NA][NCH];
     int host = -1, done_host = -1;
